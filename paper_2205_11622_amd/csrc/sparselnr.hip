@@ -13,6 +13,7 @@
 #include "sparselnr.h"
 #include "walker.hpp"
 #include "epilogue.hpp"
+#include "batch.hpp"
 
 namespace {
 
@@ -30,7 +31,8 @@ constexpr int kWalkBlock = 64;
 constexpr int kMinChunk = 64;     // smallest merge-path slice per worker (see slice_count)
 constexpr int kXcds = 8;          // MI355X deals blocks over 8 XCDs
 constexpr int kGridFactor = 8;    // resident grids per walk launch for large inputs
-constexpr int kGenericLT = 4;     // generic path: 4 x 64 = 256 columns per tile
+constexpr int kBatchTile = 64;    // batch walk: at most 64 float4 columns per tile
+constexpr int kBatchL = 512;      // batch walk: at most 512 columns of A per launch
 // <SpMMH, GEMM>: C .* D is formed once when nnz >= kHoistRatio * M (12 M J
 // bytes for the product against 4 J bytes per nonzero for a second gather).
 constexpr int64_t kHoistRatio = 3;
@@ -148,7 +150,7 @@ using KernelFn = void (*)(WalkArgs);
 struct Variant {
   KernelFn fn = nullptr;
   int W = 64;          // lanes per worker
-  bool generic = true; // generic kernel (l-tiles of 256 columns)
+  bool batch = true;   // batch walk (launches of at most kBatchL columns)
   size_t lds = 0;      // dynamic LDS bytes per block (the epilogue matrix)
   int block = kBlock;  // threads per block
   KernelFn fn_small = nullptr;  // same mapping, for inputs that fit one resident grid
@@ -156,6 +158,7 @@ struct Variant {
   int W_wide = 64;
   KernelFn fn_fine = nullptr;   // same mapping, for grids of at least fine_factor resident grids
   int fine_factor = 0;
+  int tk = 1, tl = 1;  // batch walk: float4 columns of a tile
 };
 
 template <int MODE, int W, int NB, int KV, int LV, int SCHED = slnr::kPipelined, int U = 1>
@@ -163,7 +166,7 @@ Variant fast() {
   Variant v;
   v.fn = slnr::walk_fast<MODE, W, NB, KV, LV, SCHED, U>;
   v.W = W;
-  v.generic = false;
+  v.batch = false;
   v.block = kWalkBlock;
   return v;
 }
@@ -176,7 +179,7 @@ Variant epi() {
   Variant v;
   v.fn = slnr::walk_epi<MODE, W, LV, HAD, TR, slnr::kPipelined, 1>;
   v.W = W;
-  v.generic = false;
+  v.batch = false;
   constexpr int TS = W * LV + 4;
   v.lds = (size_t)(kBlock / 64) * TR * (TS * sizeof(float) + sizeof(uint64_t));
   return v;
@@ -189,7 +192,7 @@ Variant epi_wl(int64_t Lout, int block) {
   Variant v;
   v.fn = slnr::walk_epi<MODE, W, LV, HAD, TR, slnr::kPipelined, 1, 1>;
   v.W = W;
-  v.generic = false;
+  v.batch = false;
   v.block = block;
   constexpr int LIN = W * LV;
   constexpr int TS = LIN + 4;
@@ -199,12 +202,26 @@ Variant epi_wl(int64_t Lout, int block) {
   return v;
 }
 
+// float4 columns of the equal tiles of a width.
+int batch_tile(int64_t width) {
+  const int64_t q4 = (width + 3) / 4, n = (q4 + kBatchTile - 1) / kBatchTile;
+  return n ? (int)((q4 + n - 1) / n) : 1;
+}
+
+// The batch walk, for any widths and alignment.  Its row offsets are 32-bit
+// products of 24-bit factors while the gathered arrays are below 4 GiB and
+// have fewer than 2^24 rows.
 template <int MODE>
-Variant generic() {
+Variant batch(int64_t M, int64_t K, int64_t L) {
+  const bool tail = K % 4 != 0 || L % 4 != 0;
+  const bool big = !offsets32(M, K) || !offsets32(M, L) || M >= ((int64_t)1 << 24);
   Variant v;
-  v.fn = slnr::walk_generic<MODE, kGenericLT>;
+  v.fn = big ? (tail ? slnr::walk_batch<MODE, true, true> : slnr::walk_batch<MODE, false, true>)
+             : (tail ? slnr::walk_batch<MODE, true, false> : slnr::walk_batch<MODE, false, false>);
   v.W = 64;
-  v.generic = true;
+  v.block = kWalkBlock;
+  v.tk = batch_tile(K);
+  v.tl = batch_tile(L < kBatchL ? L : kBatchL);
   return v;
 }
 
@@ -313,7 +330,7 @@ template <int K, int L>
 Variant fused_fast() {
   constexpr FusedMap m = fused_map(K, L);
   if constexpr (m.W == 0) {
-    return generic<kFused>();
+    return Variant{};
   } else {
     return fast<kFused, m.W, m.NB, m.KV, m.LV, kFS, m.U>();
   }
@@ -328,7 +345,7 @@ Variant fused_fast_l(int64_t L) {
     case 128: return fused_fast<K, 128>();
     case 256: return fused_fast<K, 256>();
     case 512: return fused_fast<K, 512>();
-    default: return generic<kFused>();
+    default: return Variant{};
   }
 }
 
@@ -336,7 +353,8 @@ Variant fused_fast_l(int64_t L) {
 // 16-byte aligned operands.  The widths of the benchmark workloads (K = L = 32, 64,
 // 128, 256 and K = 16, L = 256) keep their measured schedules; other
 // widths take the mapping of fused_map.
-Variant pick_fused(int64_t K, int64_t L, bool al) {
+Variant pick_fused(int64_t M, int64_t K, int64_t L, bool al) {
+  Variant v;
   if (al) {
     if (K == 32 && L == 32) return with_small(fast<kFused, 8, 1, 4, 4, kFS, kPU>(),
                                               slnr::walk_fast<kFused, 8, 1, 4, 4, kSmall32, kPUs>);
@@ -349,19 +367,19 @@ Variant pick_fused(int64_t K, int64_t L, bool al) {
     if (K == 16 && L == 256)
       return with_fine<kFused, 64, 16, 4, 4, 16>(fast<kFused, 64, 16, 4, 4, kFS, 16>(), 24);
     switch (K) {
-      case 16: return fused_fast_l<16>(L);
-      case 32: return fused_fast_l<32>(L);
-      case 64: return fused_fast_l<64>(L);
-      case 128: return fused_fast_l<128>(L);
-      case 256: return fused_fast_l<256>(L);
-      case 512: return fused_fast_l<512>(L);
+      case 16: v = fused_fast_l<16>(L); break;
+      case 32: v = fused_fast_l<32>(L); break;
+      case 64: v = fused_fast_l<64>(L); break;
+      case 128: v = fused_fast_l<128>(L); break;
+      case 256: v = fused_fast_l<256>(L); break;
+      case 512: v = fused_fast_l<512>(L); break;
       default: break;
     }
   }
-  return generic<kFused>();
+  return v.fn ? v : batch<kFused>(M, K, L);
 }
 
-Variant pick_sddmm(int64_t K, bool al) {
+Variant pick_sddmm(int64_t M, int64_t K, bool al) {
   if (al) {
     if (K == 16) return fast<kSddmm, 64, 16, 4, 4, kUS, 16>();
     if (K == 32) return fast<kSddmm, 8, 1, 4, 4, kUS, kPU>();
@@ -371,10 +389,10 @@ Variant pick_sddmm(int64_t K, bool al) {
     if (K == 256) return fast<kSddmm, 64, 1, 4, 4, kUS, kPU>();
     if (K == 512) return fast<kSddmm, 64, 1, 8, 4, kUS, kPU>();
   }
-  return generic<kSddmm>();
+  return batch<kSddmm>(M, K, 0);
 }
 
-Variant pick_spmm(int64_t L, bool al) {
+Variant pick_spmm(int64_t M, int64_t L, bool al) {
   if (al) {
     if (L == 16) return fast<kSpmm, 4, 1, 4, 4, kUS, kPU>();
     if (L == 32) return fast<kSpmm, 8, 1, 4, 4, kUS, kPU>();
@@ -384,7 +402,7 @@ Variant pick_spmm(int64_t L, bool al) {
     if (L == 256) return fast<kSpmm, 64, 1, 4, 4, kUS, kPU>();
     if (L == 512) return fast<kSpmm, 64, 1, 4, 8, kUS, kPU>();
   }
-  return generic<kSpmm>();
+  return batch<kSpmm>(M, 0, L);
 }
 
 // Section 6.2 benchmarks with a per-row epilogue.  Lin (the width of the
@@ -534,7 +552,7 @@ int choose_launch(int dev, int cus, const Variant *vs, int nv, int64_t N, int fa
   int per_cu = 1;
   if ((rc = blocks_per_cu(dev, v.fn, v.block, v.lds, &per_cu)) != SPARSELNR_OK) return rc;
   for (int t = 1; t < nv; ++t) {
-    if (vs[t].W != v.W || vs[t].block != v.block || vs[t].generic != v.generic)
+    if (vs[t].W != v.W || vs[t].block != v.block || vs[t].batch != v.batch)
       return SPARSELNR_ERR_UNSUPPORTED;  // alternatives must split the matrix alike
     int pc = 1;
     if ((rc = blocks_per_cu(dev, vs[t].fn, vs[t].block, vs[t].lds, &pc)) != SPARSELNR_OK)
@@ -597,8 +615,8 @@ int run_walk(Mode mode, const Variant *vs, const WalkArgs *as, int nv, hipStream
   Variant v;
   Grid g;
   if ((rc = choose_launch(dev, cus, vs, nv, a.N, 0, &v, &g)) != SPARSELNR_OK) return rc;
-  const int64_t tiles = vs[0].generic ? (a.L + 64 * kGenericLT - 1) / (64 * kGenericLT) : 1;
-  const int64_t tile_w = vs[0].generic ? 64 * kGenericLT : a.L;
+  const int64_t tile_w = vs[0].batch && a.L > kBatchL ? kBatchL : a.L;
+  const int64_t tiles = vs[0].batch && a.L > kBatchL ? (a.L + kBatchL - 1) / kBatchL : 1;
   if (fixed && mode != kSddmm) {
     while (carry_size(g, tile_w).total() > fixed->bytes && g.factor > 1)
       if ((rc = choose_launch(dev, cus, vs, nv, a.N, g.factor / 2, &v, &g)) != SPARSELNR_OK)
@@ -609,6 +627,8 @@ int run_walk(Mode mode, const Variant *vs, const WalkArgs *as, int nv, hipStream
   a.min_chunk = kMinChunk;
   a.xcd_span = g.xcd_span;
   a.xcds = kXcds;
+  a.tk = v.tk;
+  a.tl = v.tl;
   if (mode != kSddmm) {
     const CarrySize cs = carry_size(g, tile_w);
     void *ws = nullptr;
@@ -636,6 +656,8 @@ int run_walk(Mode mode, const Variant *vs, const WalkArgs *as, int nv, hipStream
       ak.meta = a.meta;
       ak.l0 = a.l0;
       ak.Lw = a.Lw;
+      ak.tk = a.tk;
+      ak.tl = a.tl;
       const Variant &vk = k == 0 ? v : vs[k];  // v: the kernel chosen for this input
       hipLaunchKernelGGL(vk.fn, dim3(g.blocks), dim3(vk.block), vk.lds, stream, ak);
       hipError_t e = hipGetLastError();
@@ -802,7 +824,7 @@ int sparselnr_fused_sddmm_spmm(const int32_t *rowptr, const int32_t *colidx,
   a.D = D;
   a.E = E;
   a.out = A;
-  return run_walk(kFused, pick_fused(K, L, al), a, (hipStream_t)stream);
+  return run_walk(kFused, pick_fused(M, K, L, al), a, (hipStream_t)stream);
 }
 
 int sparselnr_fused_sddmm_spmm_noalloc(const int32_t *rowptr, const int32_t *colidx,
@@ -823,7 +845,7 @@ int sparselnr_fused_sddmm_spmm_noalloc(const int32_t *rowptr, const int32_t *col
   a.D = D;
   a.E = E;
   a.out = A;
-  return run_walk(kFused, pick_fused(K, L, al), a, (hipStream_t)stream, &fb);
+  return run_walk(kFused, pick_fused(M, K, L, al), a, (hipStream_t)stream, &fb);
 }
 
 int sparselnr_sddmm(const int32_t *rowptr, const int32_t *colidx, const float *vals,
@@ -841,7 +863,7 @@ int sparselnr_sddmm(const int32_t *rowptr, const int32_t *colidx, const float *v
   a.C = C;
   a.D = D;
   a.out = Y;
-  return run_walk(kSddmm, pick_sddmm(K, al), a, (hipStream_t)stream);
+  return run_walk(kSddmm, pick_sddmm(M, K, al), a, (hipStream_t)stream);
 }
 
 int sparselnr_spmm(const int32_t *rowptr, const int32_t *colidx, const float *Y,
@@ -857,7 +879,7 @@ int sparselnr_spmm(const int32_t *rowptr, const int32_t *colidx, const float *Y,
   WalkArgs a = base_args(rowptr, colidx, Y, N, 0, L);
   a.E = E;
   a.out = A;
-  return run_walk(kSpmm, pick_spmm(L, al), a, (hipStream_t)stream);
+  return run_walk(kSpmm, pick_spmm(M, L, al), a, (hipStream_t)stream);
 }
 
 int sparselnr_unfused_sddmm_spmm(const int32_t *rowptr, const int32_t *colidx,

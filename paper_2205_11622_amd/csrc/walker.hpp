@@ -87,6 +87,7 @@ struct WalkArgs {
   // kGateSparse only if nnz < gate_nnz.  A closed launch exits at once.
   int64_t gate_nnz;
   int32_t gate;
+  int32_t tk, tl;     // batch walk: float4 columns of a tile of C / D and of E / A
 };
 
 enum Gate : int { kGateNone = 0, kGateDense = 1, kGateSparse = 2 };
@@ -714,70 +715,6 @@ __global__ __launch_bounds__(256) void walk_fast(WalkArgs a) {
     ++i;
   }
   if (MODE != kSddmm && glane == 0) {
-    meta[0] = s.i1 < N ? (int32_t)s.i1 : -1;
-    meta[1] = s.head ? (int32_t)s.i0 : -1;
-  }
-}
-
-// -------------------------------------------------------- generic kernel
-//
-// Any K and any l-tile of up to 64 * LT columns: one wave per worker, one
-// nonzero at a time, scalar loads.  Used when K or L has no fast variant or
-// the operands are not 16-byte aligned.
-template <int MODE, int LT>
-__global__ __launch_bounds__(256) void walk_generic(WalkArgs a) {
-  const int lane = threadIdx.x & 63;
-  const Slice s = make_slice<64>(a);
-  if (!s.active) return;
-  const int64_t worker = s.id;  // carry slots and metadata are per slice
-  int32_t *meta = a.meta + 2 * worker;
-  const int32_t *__restrict__ rowptr = a.rowptr;
-  const int64_t K = a.K, L = a.L, N = a.N, Lw = a.Lw, l0 = a.l0;
-  int64_t i = s.i0, p = s.p0;
-  while (true) {
-    const bool has_end = i < s.i1;
-    if (!has_end && i >= N) break;
-    const int64_t r_end = has_end ? (int64_t)rowptr[i + 1] : s.p1;
-    float acc[LT];
-#pragma unroll
-    for (int t = 0; t < LT; ++t) acc[t] = 0.f;
-    for (; p < r_end; ++p) {
-      const int64_t j = a.colidx[p];
-      float y;
-      if (MODE == kSpmm) {
-        y = a.vals[p];
-      } else {
-        float t = 0.f;
-        for (int64_t k = lane; k < K; k += 64) t = fmaf(a.C[i * K + k], a.D[j * K + k], t);
-        t = group_sum<64>(t);
-        y = a.vals[p] * t;
-      }
-      if (MODE == kSddmm) {
-        if (lane == 0) a.out[p] = y;
-      } else {
-#pragma unroll
-        for (int t = 0; t < LT; ++t) {
-          const int64_t l = lane + 64 * t;
-          if (l < Lw) acc[t] = fmaf(y, a.E[j * L + l0 + l], acc[t]);
-        }
-      }
-    }
-    if (MODE != kSddmm) {
-      float *dst;
-      int64_t stride_base;
-      if (!has_end) { dst = a.carry; stride_base = (worker * 2 + 1) * Lw; }
-      else if (i == s.i0 && s.head) { dst = a.carry; stride_base = (worker * 2) * Lw; }
-      else { dst = a.out; stride_base = i * L + l0; }
-#pragma unroll
-      for (int t = 0; t < LT; ++t) {
-        const int64_t l = lane + 64 * t;
-        if (l < Lw) dst[stride_base + l] = acc[t];
-      }
-    }
-    if (!has_end) break;
-    ++i;
-  }
-  if (MODE != kSddmm && lane == 0) {
     meta[0] = s.i1 < N ? (int32_t)s.i1 : -1;
     meta[1] = s.head ? (int32_t)s.i0 : -1;
   }

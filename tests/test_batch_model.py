@@ -1,0 +1,134 @@
+"""Host model of the batch walk (csrc/batch.hpp): the batches of a
+slice, the rowptr windows and the passes over row segments, re-enacted on many
+CSR shapes.  Every nonzero of a slice is passed once, in a pass of its own
+row; every row end is written exactly once, partial rows go through the
+slice's own slots, and every index stays inside its array."""
+import numpy as np
+import pytest
+
+from tests.test_partition import slice_bounds, slice_len, snap_len
+
+
+class Walk:
+    def __init__(self, rowptr, N, i0, p0, i1, p1, cap):
+        self.rp, self.N, self.i0, self.p0, self.i1, self.p1 = rowptr, N, i0, p0, i1, p1
+        self.cap = cap
+        self.head = i0 < i1 and p0 > rowptr[i0]
+        self.rlast = i1 if i1 < N else i1 - 1
+
+    def window(self, rb):
+        ws, we = [], []
+        for lane in range(64):
+            r = rb + lane
+            if r <= self.rlast:
+                assert 0 <= r < self.N  # reads rowptr[r], rowptr[r + 1]
+                ws.append(max(int(self.rp[r]), self.p0))
+                we.append(min(int(self.rp[r + 1]), self.p1))
+            else:
+                ws.append(0)
+                we.append(0)
+        return ws, we
+
+    def passes(self, ib, pb, pe, npp):
+        """Yields (p, n, row, first, last, cont, open)."""
+        rb = ib
+        while True:
+            ws, we = self.window(rb)
+            for b in range(64):
+                s, e = max(ws[b], pb), min(we[b], pe)
+                p = s
+                while p < e:
+                    n = min(npp, e - p)
+                    row = rb + b
+                    yield (p, n, row, p == s, p + n == e, ws[b] < pb,
+                           row == self.i1 or we[b] > pe)
+                    p += n
+            if not (rb + 63 < self.rlast and we[63] < pe):
+                return
+            rb += 64
+
+    def run(self, npp, y, A, written, slots):
+        """One column: A[row] or the slice's head / tail slot gets the sums."""
+        dest = lambda r: "t" if r == self.i1 else "h" if r == self.i0 and self.head else r  # noqa: E731
+
+        def put(d, v):
+            if isinstance(d, str):
+                slots[d] = v
+            else:
+                assert written[d] == 0
+                A[d], written[d] = v, 1
+
+        for rb in range(self.i0, self.rlast + 1, 64):
+            ws, we = self.window(rb)
+            for b in range(64):
+                if rb + b <= self.rlast and rb + b != self.i1 and we[b] <= ws[b]:
+                    put(dest(rb + b), 0.0)
+        ib, pb, seen = self.i0, self.p0, []
+        while pb < self.p1:
+            pe = min(self.p1, pb + self.cap)
+            acc = 0.0
+            for p, n, row, first, last, cont, opened in self.passes(ib, pb, pe, npp):
+                assert pb <= p and p + n <= pe and p + n - pb <= self.cap
+                assert self.rp[row] <= p and p + n <= self.rp[row + 1]
+                if first:
+                    assert acc == 0.0
+                seen += range(p, p + n)
+                acc += float(y[p:p + n].sum())
+                if last:
+                    if cont:
+                        acc += slots["t"]
+                    if opened:
+                        slots["t"] = acc
+                    else:
+                        put(dest(row), acc)
+                    acc = 0.0
+            if pe < self.p1:
+                while ib <= self.rlast:
+                    _, we = self.window(ib)
+                    m = [b for b in range(64) if ib + b <= self.rlast and we[b] > pe]
+                    if m:
+                        ib += m[0]
+                        break
+                    ib += 64
+                assert ib <= self.rlast
+            pb = pe
+        assert seen == list(range(self.p0, self.p1))
+        if self.i1 < self.N and self.p1 <= self.rp[self.i1]:
+            slots["t"] = 0.0
+
+
+def shapes():
+    rng = np.random.default_rng(7)
+    out = {"one": [1], "empty": [0] * 200, "none_then_one": [0] * 130 + [1], "long": [0, 5000, 0, 0, 3],
+           "ones": [1] * 700, "hub_mid": [2] * 90 + [9000] + [0] * 70 + [1] * 5,
+           # a slice that ends at the start of a long row, after rows that cross batches
+           "empty_tail": [99] * 10 + [2999], "window_edges": ([3] * 63 + [0]) * 6 + [70] * 130,
+           "power": np.minimum((rng.pareto(1.1, 1500) * 3 * (rng.random(1500) < 0.6)).astype(int), 4000)}
+    return out.items()
+
+
+@pytest.mark.parametrize("cap", [64, 512])
+@pytest.mark.parametrize("workers", [1, 4, 7, 200])
+@pytest.mark.parametrize("name,lengths", shapes())
+def test_every_nonzero_and_row_once(name, lengths, workers, cap):
+    rowptr = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int64)
+    N, nnz = len(lengths), int(rowptr[-1])
+    y = np.random.default_rng(1).integers(1, 9, nnz).astype(float)
+    S = slice_len(N + nnz, workers, 64, N=N, nnz=nnz)
+    ns = -(-(N + nnz) // S)
+    bounds = [slice_bounds(rowptr, N, nnz, S, min(k * S, N + nnz), snap_len(S)) for k in range(ns + 1)]
+    for npp in (1, 8, 16):
+        A, written, open_row = np.zeros(N), np.zeros(N, int), None
+        for (i0, p0), (i1, p1) in zip(bounds, bounds[1:]):
+            w, slots = Walk(rowptr, N, i0, p0, i1, p1, cap), {}
+            w.run(npp, y, A, written, slots)
+            if w.head:  # the row that earlier slices left open ends here
+                assert open_row is not None and open_row[0] == i0 and written[i0] == 0
+                A[i0], written[i0] = open_row[1] + slots["h"], 1
+                open_row = None
+            if i1 < N:
+                assert "t" in slots
+                base = open_row[1] if open_row and open_row[0] == i1 else 0.0
+                open_row = (i1, base + slots["t"])
+        assert written.all()
+        assert np.array_equal(A, [y[a:b].sum() for a, b in zip(rowptr, rowptr[1:])])
