@@ -31,7 +31,7 @@
  * Conventions shared by every compute entry point:
  *   - All array pointers are DEVICE pointers owned by the caller; the library
  *     never frees or retains them.  The base pointers must be 4-byte aligned;
- *     16-byte alignment with K and L multiples of 4 enables the fast paths.
+ *     16-byte alignment of all of them enables the kernels of fixed width.
  *   - Calls are asynchronous on `stream` (a hipStream_t; NULL is the null
  *     stream).  No call synchronises with the host.
  *   - Columns within a row may be unsorted and may repeat (repeats add).
@@ -254,8 +254,8 @@ SPARSELNR_API int sparselnr_last_hip_error(void);
  * taking one merge-path slice of rows + nonzeros, so a larger factor gives
  * more, shorter slices: the workers resident at one moment then cover a
  * narrower band of rows, which changes how D and E rows are shared in the
- * caches.  factor 0 restores the automatic choice (8 when the matrix has at
- * least 8 rows per resident worker, else 1); 1..64 fixes the factor for every
+ * caches.  factor 0 restores the automatic choice (by the number of rows per
+ * resident worker and the widths; 1 for small matrices); 1..64 fixes the factor for every
  * later call in the process, on every device and stream (the environment
  * variable SPARSELNR_GRID_FACTOR gives the first value).  Results are
  * deterministic for a fixed factor; another factor splits rows between slices

@@ -1,23 +1,28 @@
 // Device code of the batch walk of the fused SDDMM->SpMM library for gfx950:
-// the kernel for widths without a variant of their own, for operands off 16
-// bytes, and for arrays of 4 GiB and more.
+// the kernel for any width, alignment and array size.
 //
 // A wave takes a merge-path slice (walker.hpp) in batches of kBatch nonzeros,
-// whose columns it copies to LDS.  In one pass over the rows of the batch it
-// forms the dot products, y = b * dot(C_i, D_j), beside the columns in LDS; in
-// a second pass it adds y * E_j into the rows of A.  In both passes G lanes
-// take four floats each of a gathered row, so 64 / G nonzeros of one row go
-// side by side, and U such groups of gathers are issued before the first is
-// used.  Lane count and column tile depend on the width alone, at run time:
-// every width from 1 to 256 floats takes one tile, a wider one equal tiles.
+// whose columns and values it copies to LDS.  In one pass over the rows of the
+// batch it forms y = b * dot(C_i, D_j) beside the columns in LDS; in a second
+// pass it adds y * E_j into the rows of A.  In both passes G lanes take four
+// floats each of a gathered row, so 64 / G nonzeros go side by side, and four
+// such gathers are issued before the first is used: of one row, or of two or
+// four short rows at once.  Lane count and column tile depend on the width
+// alone, at run time: every width from 1 to 256 floats takes one tile, a wider
+// one equal tiles.
 //
-// What bounds it is the fabric that the L2 misses go through: at 100003
-// power-law rows of 25 nonzeros, K = 100, L = 47, 16M lines of 128 bytes are
-// touched (6.5 per nonzero, as rows straddle lines) in 267 us, 60 lines a
-// nanosecond, where plain streaming walks reach 58.  One nonzero at a time
-// with one float per lane, which this kernel replaces, took 564 us; SpMM of
-// 300007 rows of 20 nonzeros at L = 96: 843 -> 331 us; K = 259, L = 261 at
-// 20011 rows of 11: 410 -> 113 us.
+// What bounds it is the fabric that the L2 misses go through (plain streaming
+// walks reach 58 lines of 128 bytes a nanosecond) and, for rows of a few
+// nonzeros, the instructions per row.  Measured on MI355X, us:
+//   one nonzero at a time, one float per lane (what odd widths had) -> batch:
+//     100003 power-law rows of 25, K = 100, L = 47: 604 -> 267 (16M lines touched, 60 a ns)
+//     SpMM, 300007 power-law rows of 20, L = 96: 894 -> 334
+//   lane groups of a wave walking rows of their own (powers of two had) -> batch:
+//     150000 uniform rows of 24 at K = L = 64, D transposed first: 320 -> 269
+//     2^16 R-MAT vertices of 20 at K = L = 16: 165 -> 55, at 64: 125 -> 73
+//     27-point stencil of 101^3 at K = L = 64: 1815 -> 1020
+//   whose groups wait for the longest row among them, and whose burst of one row
+//   ends before the next begins.
 #pragma once
 
 #include "walker.hpp"
@@ -30,6 +35,7 @@ constexpr int kBatch = 512;
 
 typedef float f4u_t __attribute__((ext_vector_type(4), aligned(4)));
 typedef unsigned int u2_t __attribute__((ext_vector_type(2)));
+typedef int i4_t __attribute__((ext_vector_type(4)));
 
 // v plus the value of the 16-lane row beside it (rows 0-1, 2-3), in all lanes.
 __device__ __forceinline__ float add_row16(float v) {
@@ -62,11 +68,50 @@ __device__ __forceinline__ float lanes_sum(float v) {
 // Sum over the groups: lanes of equal (lane & (G - 1)); valid in group 0.
 template <int G>
 __device__ __forceinline__ float groups_sum(float v) {
+  if constexpr (G <= 32) v = add_half(v);
+  if constexpr (G <= 16) v = add_row16(v);
   if constexpr (G <= 4) v += dpp<0x124>(v);  // row_ror:4
   if constexpr (G <= 8) v += dpp<0x128>(v);  // row_ror:8
-  if constexpr (G <= 16) v = add_row16(v);
-  if constexpr (G <= 32) v = add_half(v);
   return v;
+}
+
+// The two values' sums over halves: x in the lower half of the wave, y in the
+// upper.
+__device__ __forceinline__ float add_halves(float x, float y) {
+  const u2_t r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, x),
+                                                  __builtin_bit_cast(unsigned, y), false, false);
+  const unsigned lo = r[0], hi = r[1];
+  return __builtin_bit_cast(float, lo) + __builtin_bit_cast(float, hi);
+}
+
+// groups_sum of two (R = 2) or four (R = 4) values at once, each formed in the
+// same order: the exchange of halves forms two of them in one instruction, that
+// of 16-lane rows four, so four rows of A take 8 instructions instead of 32.
+// value_of() says which value's sum a lane's part of the wave (of 64 / R lanes)
+// holds, in its first G lanes.
+template <int R, int G>
+__device__ __forceinline__ float groups_sum_of(const float (&x)[R][4], int c) {
+  static_assert(G <= 64 / R, "a group inside a part");
+  float v = add_halves(x[0][c], x[1][c]);
+  if constexpr (R == 4) {
+    const float w = add_halves(x[2][c], x[3][c]);
+    const u2_t r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, v),
+                                                    __builtin_bit_cast(unsigned, w), false, false);
+    const unsigned lo = r[0], hi = r[1];
+    v = __builtin_bit_cast(float, lo) + __builtin_bit_cast(float, hi);
+  } else if constexpr (G <= 16) {
+    v = add_row16(v);
+  }
+  if constexpr (G <= 4) v += dpp<0x124>(v);
+  if constexpr (G <= 8) v += dpp<0x128>(v);
+  return v;
+}
+
+template <int R>
+__device__ __forceinline__ int value_of(int lane) {
+  if constexpr (R == 2) return lane >> 5;
+  const int k = lane >> 4;  // the 16-lane rows hold values 0, 2, 1, 3
+  return ((k & 1) << 1) | (k >> 1);
 }
 
 // Floats col .. col+3 of row j; of a row too narrow for that (not `wide`) only
@@ -118,161 +163,250 @@ struct BatchWalk {
     if (!in) ws = we = 0;
   }
 
-  // f(row, s, e, cont, open) for every row with nonzeros s .. e-1 in the
-  // batch [pb, pe); cont / open: it has nonzeros in an earlier batch of the
-  // slice / does not end here.
-  template <typename F>
-  __device__ __forceinline__ void for_rows(int ib, int pb, int pe, F f) {
+  // The rows with nonzeros s .. e-1 in the batch [pb, pe): several(R, rb, b, s, e)
+  // for R = 4 rows rb + b[0..3] of at most NPP nonzeros or R = 2 rows of at most
+  // 2 * NPP (four passes side by side either way), one(row, s, e) for the others.
+  // Rows of 10 nonzeros, one after another, would leave three of the four
+  // gathers of a lane unused: in sets they run 1.2-1.4x faster at K = L = 16.
+  template <int NPP, typename One, typename Several>
+  __device__ __forceinline__ void for_rows(int ib, int pb, int pe, One one, Several several) {
     for (int rb = ib;; rb += 64) {
       window(rb);
       const int vs = ws > pb ? ws : pb, ve = we < pe ? we : pe;
       uint64_t mask = __ballot(ve > vs);
+      const uint64_t tall4 = __ballot(ve - vs > NPP), tall2 = __ballot(ve - vs > 2 * NPP);
       const bool more = rb + 63 < rlast && __builtin_amdgcn_readlane(we, 63) < pe;
+      // the next R rows, if there are that many and none is in `tall`
+      auto set = [&](auto r, uint64_t tall) {
+        constexpr int R = decltype(r)::value;
+        uint64_t m = mask;
+#pragma unroll
+        for (int u = 0; u < R - 1; ++u) m &= m - 1;
+        if (m == 0) return false;
+        m &= m - 1;
+        if (((mask ^ m) & tall) != 0) return false;
+        i4_t b, s, e;
+#pragma unroll
+        for (int u = 0; u < R; ++u) {
+          const int i = __builtin_ctzll(mask);
+          mask &= mask - 1;
+          b[u] = i;
+          s[u] = __builtin_amdgcn_readlane(vs, i);
+          e[u] = __builtin_amdgcn_readlane(ve, i);
+        }
+        several(r, rb, b, s, e);
+        return true;
+      };
       while (mask) {
+        if constexpr (NPP >= 4)
+          if (set(std::integral_constant<int, 4>{}, tall4)) continue;
+        if constexpr (NPP >= 2)
+          if (set(std::integral_constant<int, 2>{}, tall2)) continue;
         const int b = __builtin_ctzll(mask);
         mask &= mask - 1;
-        const int row = rb + b;
-        f(row, __builtin_amdgcn_readlane(vs, b), __builtin_amdgcn_readlane(ve, b),
-          __builtin_amdgcn_readlane(ws, b) < pb,
-          row == i1 || __builtin_amdgcn_readlane(we, b) > pe);
+        one(rb + b, __builtin_amdgcn_readlane(vs, b), __builtin_amdgcn_readlane(ve, b));
       }
       if (!more) return;
     }
   }
 
   // Partial dot products of the batch over floats [4 * q0, 4 * q0 + 4 * nq) of
-  // the K floats: added to the y of every nonzero.
+  // the K floats: y = b * dot if `whole` (that is all of K; y holds b before),
+  // else added to y.
   template <int G>
-  __device__ __forceinline__ void dots(int ib, int pb, int pe, int q0, int nq) {
+  __device__ __forceinline__ void dots(int ib, int pb, int pe, int q0, int nq, bool whole) {
     constexpr int NPP = 64 / G, U = 4;
     int ln = lane;
     asm volatile("" : "+v"(ln));  // keeps the lane's indices out of the registers of other phases
     const int g = ln / G, q = ln & (G - 1);
-    const int first = 4 * (q0 + q);
     const bool lane_in = q < nq;
+    const int first = 4 * (q0 + (lane_in ? q : nq - 1));  // lanes past nq repeat the last one's loads
     const int valid = a.K - first;
     // the last lane of a ragged width reads the last four floats and drops
     // those that the lane before it has
     const int col = TAIL && valid < 4 && a.K >= 4 ? a.K - 4 : first;
     const int drop = first - col;
-    for_rows(ib, pb, pe, [&](int row, int s, int e, bool, bool) {
-      float c[4] = {0.f, 0.f, 0.f, 0.f};
-      if (lane_in) ld_cols<TAIL, true>(c, a.C, row, a.K, col, a.K >= 4, valid);
-      for (int k = s; k < e; k += U * NPP) {
-        const int n = e - k;
-        int2 *zp = nz + (k - pb);
-        int2 z[U];
-        float x[U][4];
-        auto finish = [&](int u, int idx) {
-          float t = 0.f;
-          if constexpr (TAIL) {
+    auto load_c = [&](float (&c)[4], int row) {
+      ld_cols<TAIL, true>(c, a.C, row, a.K, col, a.K >= 4, valid);
+    };
+    auto load_d = [&](float (&x)[4], int j) {
+      ld_cols<TAIL, BIG>(x, a.D, j, a.K, col, a.K >= 4, valid);
+    };
+    // all lanes of a group hold the sum and write the same word
+    auto finish = [&](const float (&c)[4], float (&x)[4], int2 z, int2 *at) {
+      if constexpr (TAIL) {
 #pragma unroll
-            for (int v = 0; v < 3; ++v) x[u][v] = v < drop ? 0.f : x[u][v];
-          }
-#pragma unroll
-          for (int v = 0; v < 4; ++v) t = fmaf(c[v], x[u][v], t);
-          t = lanes_sum<G>(lane_in ? t : 0.f);
-          if (q == 0) zp[idx].y = __builtin_bit_cast(int, __builtin_bit_cast(float, z[u].y) + t);
-        };
-        if (n >= U * NPP) {
-#pragma unroll
-          for (int u = 0; u < U; ++u) z[u] = zp[u * NPP + g];
-          if (lane_in) {
-#pragma unroll
-            for (int u = 0; u < U; ++u) ld_cols<TAIL, BIG>(x[u], a.D, z[u].x, a.K, col, a.K >= 4, valid);
-          }
-#pragma unroll
-          for (int u = 0; u < U; ++u) finish(u, u * NPP + g);
-        } else {  // groups past the row's end repeat its last nonzero
-          auto at = [&](int u) { return u * NPP + g < n ? u * NPP + g : n - 1; };
-#pragma unroll
-          for (int u = 0; u < U; ++u)
-            if (u * NPP < n) z[u] = zp[at(u)];
-          if (lane_in) {
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-              if (u * NPP < n) ld_cols<TAIL, BIG>(x[u], a.D, z[u].x, a.K, col, a.K >= 4, valid);
-          }
-#pragma unroll
-          for (int u = 0; u < U; ++u)
-            if (u * NPP < n) finish(u, at(u));
-        }
+        for (int v = 0; v < 3; ++v) x[v] = v < drop ? 0.f : x[v];
       }
-    });
+      float t = 0.f;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) t = fmaf(c[v], x[v], t);
+      t = lanes_sum<G>(lane_in ? t : 0.f);
+      const float y = __builtin_bit_cast(float, z.y);
+      at->y = __builtin_bit_cast(int, whole ? y * t : y + t);
+    };
+    for_rows<NPP>(
+        ib, pb, pe,
+        [&](int row, int s, int e) {
+          float c[4];
+          load_c(c, row);
+          for (int k = s; k < e; k += U * NPP) {
+            const int n = e - k;
+            int2 *zp = nz + (k - pb);
+            int2 z[U];
+            float x[U][4];
+            if (n >= U * NPP) {
+#pragma unroll
+              for (int u = 0; u < U; ++u) z[u] = zp[u * NPP + g];
+#pragma unroll
+              for (int u = 0; u < U; ++u) load_d(x[u], z[u].x);
+#pragma unroll
+              for (int u = 0; u < U; ++u) finish(c, x[u], z[u], zp + (u * NPP + g));
+            } else {  // groups past the row's end repeat its last nonzero
+              auto at = [&](int u) { return u * NPP + g < n ? u * NPP + g : n - 1; };
+#pragma unroll
+              for (int u = 0; u < U; ++u)
+                if (u * NPP < n) z[u] = zp[at(u)];
+#pragma unroll
+              for (int u = 0; u < U; ++u)
+                if (u * NPP < n) load_d(x[u], z[u].x);
+#pragma unroll
+              for (int u = 0; u < U; ++u)
+                if (u * NPP < n) finish(c, x[u], z[u], zp + at(u));
+            }
+          }
+        },
+        [&](auto r, int rb, i4_t b, i4_t s, i4_t e) {
+          constexpr int R = decltype(r)::value, S = U / R;  // S passes a row
+          int2 *zp[U];
+          int2 z[U];
+          float c[R][4], x[U][4];
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            const int n = e[u / S] - s[u / S], k = u % S * NPP + g;
+            zp[u] = nz + (s[u / S] - pb + (k < n ? k : n - 1));
+            z[u] = *zp[u];
+          }
+#pragma unroll
+          for (int u = 0; u < R; ++u) load_c(c[u], rb + b[u]);
+#pragma unroll
+          for (int u = 0; u < U; ++u) load_d(x[u], z[u].x);
+#pragma unroll
+          for (int u = 0; u < U; ++u) finish(c[u / S], x[u], z[u], zp[u]);
+        });
   }
 
-  // Columns l0 + [4 * q0, 4 * q0 + 4 * nq) of the rows of the batch.
+  // Columns l0 + [4 * q0, 4 * q0 + 4 * nq) of the rows of the batch.  crow: the
+  // row begun in an earlier batch of the slice, orow: the one that goes on in
+  // a later batch (-1: none).
   template <int G>
-  __device__ __forceinline__ void rows(int ib, int pb, int pe, int q0, int nq) {
+  __device__ __forceinline__ void rows(int ib, int pb, int pe, int q0, int nq, int crow, int orow) {
     constexpr int NPP = 64 / G, U = 4;
     int ln = lane;
-    asm volatile("" : "+v"(ln));  // keeps the lane's indices out of the registers of other phases
+    asm volatile("" : "+v"(ln));
     const int g = ln / G, q = ln & (G - 1);
-    const int first = 4 * (q0 + q);
     const bool lane_in = q < nq;
+    const int first = 4 * (q0 + (lane_in ? q : nq - 1));
     const int valid = a.Lw - first;
     // the last lane of a ragged width takes the last four columns: it forms
     // and stores the same values as its neighbour where they overlap
     const int col = TAIL && valid < 4 && a.Lw >= 4 ? a.Lw - 4 : first;
-    for_rows(ib, pb, pe, [&](int row, int s, int e, bool cont, bool open) {
-      float acc[4] = {0.f, 0.f, 0.f, 0.f};
-      for (int k = s; k < e; k += U * NPP) {
-        const int n = e - k;
-        const int2 *zp = nz + (k - pb);
-        int2 z[U];
-        float x[U][4];
-        auto add = [&](int u) {
+    auto load_e = [&](float (&x)[4], int j) {
+      ld_cols<TAIL, BIG>(x, a.E, j, a.L, a.l0 + col, a.Lw >= 4, valid);
+    };
+    auto store = [&](float *dst, const float (&r)[4]) {
+      if (!TAIL || a.Lw >= 4) {
+        f4u_t o;
+        o[0] = r[0]; o[1] = r[1]; o[2] = r[2]; o[3] = r[3];
+        *reinterpret_cast<f4u_t *>(dst) = o;
+      } else {
 #pragma unroll
-          for (int v = 0; v < 4; ++v)
-            acc[v] = fmaf(__builtin_bit_cast(float, z[u].y), x[u][v], acc[v]);
-        };
-        if (n >= U * NPP) {
+        for (int v = 0; v < 3; ++v)
+          if (v < valid) dst[v] = r[v];
+      }
+    };
+    auto add = [&](float (&acc)[4], const float (&x)[4], int2 z) {
 #pragma unroll
-          for (int u = 0; u < U; ++u) z[u] = zp[u * NPP + g];
-          if (lane_in) {
+      for (int v = 0; v < 4; ++v) acc[v] = fmaf(__builtin_bit_cast(float, z.y), x[v], acc[v]);
+    };
+    for_rows<NPP>(
+        ib, pb, pe,
+        [&](int row, int s, int e) {
+          float acc[4] = {0.f, 0.f, 0.f, 0.f};
+          for (int k = s; k < e; k += U * NPP) {
+            const int n = e - k;
+            const int2 *zp = nz + (k - pb);
+            int2 z[U];
+            float x[U][4];
+            if (n >= U * NPP) {
 #pragma unroll
-            for (int u = 0; u < U; ++u) ld_cols<TAIL, BIG>(x[u], a.E, z[u].x, a.L, a.l0 + col, a.Lw >= 4, valid);
+              for (int u = 0; u < U; ++u) z[u] = zp[u * NPP + g];
 #pragma unroll
-            for (int u = 0; u < U; ++u) add(u);
-          }
-        } else {
+              for (int u = 0; u < U; ++u) load_e(x[u], z[u].x);
 #pragma unroll
-          for (int u = 0; u < U; ++u)
-            if (u * NPP < n) z[u] = zp[u * NPP + g < n ? u * NPP + g : n - 1];
-          if (lane_in) {
+              for (int u = 0; u < U; ++u) add(acc, x[u], z[u]);
+            } else {
 #pragma unroll
-            for (int u = 0; u < U; ++u)
-              if (u * NPP < n) ld_cols<TAIL, BIG>(x[u], a.E, z[u].x, a.L, a.l0 + col, a.Lw >= 4, valid);
+              for (int u = 0; u < U; ++u)
+                if (u * NPP < n) z[u] = zp[u * NPP + g < n ? u * NPP + g : n - 1];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-              if ((u + 1) * NPP <= n) add(u);
-              else if (u * NPP < n && u * NPP + g < n) add(u);
+              for (int u = 0; u < U; ++u)
+                if (u * NPP < n) load_e(x[u], z[u].x);
+#pragma unroll
+              for (int u = 0; u < U; ++u) {
+                if ((u + 1) * NPP <= n) add(acc, x[u], z[u]);
+                else if (u * NPP < n && u * NPP + g < n) add(acc, x[u], z[u]);
+              }
             }
           }
-        }
-      }
 #pragma unroll
-      for (int v = 0; v < 4; ++v) acc[v] = groups_sum<G>(acc[v]);
-      if (lane_in && g == 0) {
-        float *dst = open ? tail_slot + col
-                          : row == i0 && head ? head_slot + col
-                                              : a.out + (int64_t)row * a.L + a.l0 + col;
-        if (!TAIL || a.Lw >= 4) {
-          if (cont) {
-            const f4u_t o = *reinterpret_cast<const f4u_t *>(tail_slot + col);
+          for (int v = 0; v < 4; ++v) acc[v] = groups_sum<G>(acc[v]);
+          if (lane_in && g == 0) {
+            if (row == crow) {
 #pragma unroll
-            for (int v = 0; v < 4; ++v) acc[v] = o[v] + acc[v];
+              for (int v = 0; v < 4; ++v)
+                if (!TAIL || v < valid || a.Lw >= 4) acc[v] = tail_slot[col + v] + acc[v];
+            }
+            store(row == i1 || row == orow ? tail_slot + col
+                  : row == i0 && head      ? head_slot + col
+                                           : a.out + (int64_t)row * a.L + a.l0 + col,
+                  acc);
           }
-          f4u_t o;
-          o[0] = acc[0]; o[1] = acc[1]; o[2] = acc[2]; o[3] = acc[3];
-          *reinterpret_cast<f4u_t *>(dst) = o;
-        } else {
+        },
+        [&](auto r, int rb, i4_t b, i4_t s, i4_t e) {
+          constexpr int R = decltype(r)::value, S = U / R;
+          if constexpr (G <= 64 / R) {
+            int2 z[U];
+            float x[U][4], acc[R][4] = {};
 #pragma unroll
-          for (int v = 0; v < 3; ++v)
-            if (v < valid) dst[v] = (cont ? tail_slot[col + v] : 0.f) + acc[v];
-        }
-      }
-    });
+            for (int u = 0; u < U; ++u) {
+              const int n = e[u / S] - s[u / S], k = u % S * NPP + g;
+              z[u] = nz[s[u / S] - pb + (k < n ? k : n - 1)];
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) load_e(x[u], z[u].x);
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+              if (u % S * NPP + g < e[u / S] - s[u / S]) add(acc[u / S], x[u], z[u]);
+            float o[4];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) o[v] = groups_sum_of<R, G>(acc, v);
+            const int k = value_of<R>(ln);
+            int row = rb + (k == 0 ? b.x : b.y);
+            if constexpr (R == 4) row = k < 2 ? row : rb + (k == 2 ? b.z : b.w);
+            if (lane_in && (ln & (64 / R - 1)) < G) {
+              if (row == crow) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                  if (!TAIL || v < valid || a.Lw >= 4) o[v] = tail_slot[col + v] + o[v];
+              }
+              store(row == i1 || row == orow ? tail_slot + col
+                    : row == i0 && head      ? head_slot + col
+                                             : a.out + (int64_t)row * a.L + a.l0 + col,
+                    o);
+            }
+          }
+        });
   }
 
   // Zero rows (or partial rows) of the segments without a nonzero.
@@ -302,55 +436,72 @@ struct BatchWalk {
     tail_slot = head_slot + a.Lw;
     wrb = -1;
     if constexpr (MODE != kSddmm) zeros();
-    int ib = i0;
+    int ib = i0, crow = -1;
     for (int pb = p0; pb < p1;) {
       const int pe = p1 - pb < kBatch ? p1 : pb + kBatch;
       const int n = pe - pb;
-      for (int t = lane; t < n; t += 64) {
-        int2 z;
-        z.x = ld_stream(a.colidx + pb + t);
-        z.y = MODE == kSpmm ? __builtin_bit_cast(int, ld_stream(a.vals + pb + t)) : 0;
-        nz[t] = z;
+      const int qk = (a.K + 3) >> 2;
+      const bool whole = MODE == kSpmm || qk <= a.tk;  // one tile holds all of K
+      int2 z[kBatch / 64];
+#pragma unroll
+      for (int t = 0; t < kBatch / 64; ++t) {
+        const int k = t * 64 + lane;
+        z[t] = int2{0, 0};
+        if (k < n) {
+          z[t].x = ld_stream(a.colidx + pb + k);
+          if (whole) z[t].y = __builtin_bit_cast(int, ld_stream(a.vals + pb + k));
+        }
+      }
+#pragma unroll
+      for (int t = 0; t < kBatch / 64; ++t)
+        if (t * 64 + lane < n) nz[t * 64 + lane] = z[t];
+      // the first row with nonzeros from pe on, and whether it has some before
+      int inext = ib, orow = -1;
+      if (pe < p1) {
+        while (inext <= rlast) {
+          window(inext);
+          const uint64_t m = __ballot(inext + lane <= rlast && we > pe);
+          if (m) {
+            const int b = __builtin_ctzll(m);
+            inext += b;
+            if (__builtin_amdgcn_readlane(ws, b) < pe) orow = inext;
+            break;
+          }
+          inext += 64;
+        }
       }
       if constexpr (MODE != kSpmm) {
-        const int q4 = (a.K + 3) >> 2;
-        for (int q0 = 0; q0 < q4; q0 += a.tk) {
-          const int nq = q4 - q0 < a.tk ? q4 - q0 : a.tk;
-          if (nq <= 4) dots<4>(ib, pb, pe, q0, nq);
-          else if (nq <= 8) dots<8>(ib, pb, pe, q0, nq);
-          else if (nq <= 16) dots<16>(ib, pb, pe, q0, nq);
-          else if (nq <= 32) dots<32>(ib, pb, pe, q0, nq);
-          else dots<64>(ib, pb, pe, q0, nq);
+        for (int q0 = 0; q0 < qk; q0 += a.tk) {
+          const int nq = qk - q0 < a.tk ? qk - q0 : a.tk;
+          if (nq <= 4) dots<4>(ib, pb, pe, q0, nq, whole);
+          else if (nq <= 8) dots<8>(ib, pb, pe, q0, nq, whole);
+          else if (nq <= 16) dots<16>(ib, pb, pe, q0, nq, whole);
+          else if (nq <= 32) dots<32>(ib, pb, pe, q0, nq, whole);
+          else dots<64>(ib, pb, pe, q0, nq, whole);
         }
-        for (int t = lane; t < n; t += 64) {
-          const float y = ld_stream(a.vals + pb + t) * __builtin_bit_cast(float, nz[t].y);
-          if constexpr (MODE == kSddmm) a.out[pb + t] = y;
-          else nz[t].y = __builtin_bit_cast(int, y);
+        if (!whole || qk == 0 || MODE == kSddmm) {
+          for (int t = lane; t < n; t += 64) {
+            float y = __builtin_bit_cast(float, nz[t].y);
+            if (qk == 0) y *= 0.f;  // K = 0: b times an empty sum
+            else if (!whole) y *= ld_stream(a.vals + pb + t);
+            if constexpr (MODE == kSddmm) a.out[pb + t] = y;
+            else nz[t].y = __builtin_bit_cast(int, y);
+          }
         }
       }
       if constexpr (MODE != kSddmm) {
         const int q4 = (a.Lw + 3) >> 2;
         for (int q0 = 0; q0 < q4; q0 += a.tl) {
           const int nq = q4 - q0 < a.tl ? q4 - q0 : a.tl;
-          if (nq <= 4) rows<4>(ib, pb, pe, q0, nq);
-          else if (nq <= 8) rows<8>(ib, pb, pe, q0, nq);
-          else if (nq <= 16) rows<16>(ib, pb, pe, q0, nq);
-          else if (nq <= 32) rows<32>(ib, pb, pe, q0, nq);
-          else rows<64>(ib, pb, pe, q0, nq);
+          if (nq <= 4) rows<4>(ib, pb, pe, q0, nq, crow, orow);
+          else if (nq <= 8) rows<8>(ib, pb, pe, q0, nq, crow, orow);
+          else if (nq <= 16) rows<16>(ib, pb, pe, q0, nq, crow, orow);
+          else if (nq <= 32) rows<32>(ib, pb, pe, q0, nq, crow, orow);
+          else rows<64>(ib, pb, pe, q0, nq, crow, orow);
         }
       }
-      // first row with nonzeros from pe on
-      if (pe < p1) {
-        while (ib <= rlast) {
-          window(ib);
-          const uint64_t m = __ballot(ib + lane <= rlast && we > pe);
-          if (m) {
-            ib += __builtin_ctzll(m);
-            break;
-          }
-          ib += 64;
-        }
-      }
+      ib = inext;
+      crow = orow;
       pb = pe;
     }
     // A tail segment without a nonzero: its slot may hold a row carried from

@@ -32,6 +32,7 @@ constexpr int kMinChunk = 64;     // smallest merge-path slice per worker (see s
 constexpr int kXcds = 8;          // MI355X deals blocks over 8 XCDs
 constexpr int kGridFactor = 8;    // resident grids per walk launch for large inputs
 constexpr int kBatchTile = 64;    // batch walk: at most 64 float4 columns per tile
+constexpr size_t kScratchBytes = SPARSELNR_NOALLOC_SCRATCH_BYTES;  // no-allocation device array
 constexpr int kBatchL = 512;      // batch walk: at most 512 columns of A per launch
 // <SpMMH, GEMM>: C .* D is formed once when nnz >= kHoistRatio * M (12 M J
 // bytes for the product against 4 J bytes per nonzero for a second gather).
@@ -153,12 +154,13 @@ struct Variant {
   bool batch = true;   // batch walk (launches of at most kBatchL columns)
   size_t lds = 0;      // dynamic LDS bytes per block (the epilogue matrix)
   int block = kBlock;  // threads per block
-  KernelFn fn_small = nullptr;  // same mapping, for inputs that fit one resident grid
   KernelFn fn_wide = nullptr;   // wider workers, for inputs that need several resident grids
   int W_wide = 64;
   KernelFn fn_fine = nullptr;   // same mapping, for grids of at least fine_factor resident grids
   int fine_factor = 0;
   int tk = 1, tl = 1;  // batch walk: float4 columns of a tile
+  int rows = 0;        // batch walk: rows per slice that the automatic grid aims at
+  int64_t carry_row = 0;  // and bytes of carry per worker
 };
 
 template <int MODE, int W, int NB, int KV, int LV, int SCHED = slnr::kPipelined, int U = 1>
@@ -222,11 +224,13 @@ Variant batch(int64_t M, int64_t K, int64_t L) {
   v.block = kWalkBlock;
   v.tk = batch_tile(K);
   v.tl = batch_tile(L < kBatchL ? L : kBatchL);
+  v.rows = K + L < 256 ? 16 : 6;
+  v.carry_row = MODE == kSddmm ? 0 : 2 * (L < kBatchL ? L : kBatchL) * 4 + 8;
   return v;
 }
 
-// Gather schedule of the fused kernels and of the unfused (SDDMM, SpMM)
-// kernels, each set to what measured fastest for it on MI355X: the fused
+// Gather schedule of the fixed-width fused kernels and of the unfused (SDDMM,
+// SpMM) ones, each set to what measured fastest for it on MI355X: the fused
 // kernels pace their gathers (the K = 16, L = 256 one only for coarse slices,
 // see with_fine), the unfused ones pipeline them.  Nonzeros per
 // step of the paced schedule: 8 for the 128-wide rows, 4 otherwise (the
@@ -236,34 +240,18 @@ constexpr int kUS = slnr::kPipelined;
 constexpr int kPU = 4;
 constexpr int kPU128 = 8;
 
-// Inputs that fit one resident grid (few rows per worker) run with more
-// nonzeros per paced step at K = L = 32 and 64 (measured on MI355X: 8 per step
-// is 8% faster on 65536 rows of 16 nonzeros, 4 is 1% faster on R-MAT 2^22).
-constexpr int kPUs = 8;
-// Gather schedule of the small-input fused kernel at K = L = 32: all gathers
-// of a step at once.  Measured on MI355X, 2048 rows of 10 nonzeros (16-item
-// slices): 12.3 us per call against 13.2 paced.  At K = L = 64 the burst
-// walk is 5% slower on 65536 rows of 16 nonzeros, which keep 64-item slices
-// and the paced walk.
-constexpr int kSmall32 = slnr::kBurst;
-
 // The 64-lane fused kernel of large inputs at K = L = 128 takes 10 nonzeros
 // per paced step (measured on MI355X, R-MAT 2^20: 1.5-2.3% faster than 8 on
 // two boxes; 6 and 16 slower, as are 2 or 3 loads in flight per issue).
 constexpr int kPU128W = 10;
 
-Variant with_small(Variant v, KernelFn small) {
-  v.fn_small = small;
-  return v;
-}
-
 // Large inputs (several resident grids) walk with one 64-lane worker per
 // wave instead of several narrower ones.  Measured on MI355X, the fused
-// kernel and both unfused passes at K = L = 64 and 128 on R-MAT graphs with
-// 2^20 and 2^22 vertices: 1-8% faster (fewer nonzeros in flight per CU keep
-// the gathered rows of an XCD's workers closer together in L2).  Inputs
-// that fit one resident grid keep the narrow workers: on 65536 rows of 16
-// nonzeros the 64-lane walk is 35-55% slower (4x fewer workers).
+// kernel at K = L = 64 and 128 on R-MAT graphs with 2^20 and 2^22 vertices:
+// 1-8% faster (fewer nonzeros in flight per CU keep the gathered rows of an
+// XCD's workers closer together in L2).  Inputs that fit one resident grid
+// keep the narrow workers: on 65536 rows of 16 nonzeros the 64-lane walk is
+// 35-55% slower (4x fewer workers).
 template <int MODE, int KV, int LV, int SCHED, int U>
 Variant with_wide(Variant v) {
   v.fn_wide = slnr::walk_fast<MODE, 64, 1, KV, LV, SCHED, U>;
@@ -290,118 +278,50 @@ Variant with_fine(Variant v, int from) {
   return v;
 }
 
-// Lane mapping of a fused fast variant for K, L in {16, ..., 512}: the
-// consumer spreads E_j / A_i over W lanes of LV floats (L = W * LV); the
-// producer forms NB dot products per pass, each over PS = W / NB lanes of KV
-// floats (K = PS * KV).  LV is 4 (8 at L = 512) unless K is so wide against
-// L that a dot over all W lanes would need more than 16 floats per lane;
-// then the consumer takes 2 or 1 floats per lane on more lanes.  KV is 4
-// where it fits, larger when K is wide against L (one dot per pass over the
-// whole worker, at most 32 floats), 2 when 4 would need more than 64
-// registers of gathered E rows per pass.  U: nonzeros per paced step (NB for
-// the multi-dot passes, else as many as 64 registers of gathered rows allow,
-// at most 4).  W == 0: no fast variant.
-struct FusedMap {
-  int W, LV, KV, NB, U;
-};
+// The batch walk serves every width; the kernels of fixed width stay where they
+// are the faster ones (us on MI355X, fixed width / batch):
+//  * K = L = 64 and 128 with at least 1 GiB of D and E rows, 64-lane workers.
+//    R-MAT graphs: 2^22 vertices at 64 10617 / 11463, 2^21 at 64 3136 / 3449,
+//    2^20 at 128 2436 / 2566 to 2674 / 2896 by box: their hot columns crowd a few
+//    memory channels, and one gather in flight per wave crowds them least.  (Other
+//    matrices of that size lose by it: 3M uniform rows of 16 at 64 5296 / 4491.)
+//    Below 1 GiB the batch walk is ahead on all: 2^19 vertices at 64 598 / 479, 2^18
+//    at 128 582 / 520, 700001 power-law rows at 128 2508 / 2010.
+//  * K = L = 256 and K = 16, L = 256 with more than 256 MiB of them (the size of
+//    the memory-side cache): 27-point stencil of 101^3 at 256 6609 / 7196; below
+//    it 36^3 at 256 212 / 175.
+//  * SDDMM at K = 256 and SpMM at L = 256: stencil of 36^3 84 / 96, 82 / 87;
+//    elsewhere within 2%.
+//  * widths of 512 (two tiles of the batch walk, one after the other) with few
+//    rows a wave: 3000 power-law rows of 20 at K = L = 512 54 / 63, 2^13 R-MAT
+//    vertices SDDMM 24 / 36; 46656 rows 487 / 408.
+constexpr int64_t kFewRows = 16384;
 
-constexpr FusedMap fused_map(int K, int L) {
-  int LV = L == 512 ? 8 : 4;
-  while (LV > 1 && K / (L / LV) > 16) LV /= 2;
-  const int W = L / LV;
-  if (W > 64) return FusedMap{0, 0, 0, 0, 0};
-  int KV = 4;
-  while (KV <= 32 && K / KV > W) KV *= 2;
-  if (KV > 32) return FusedMap{0, 0, 0, 0, 0};
-  int PS = K / KV;
-  int NB = W / PS;
-  if (NB * LV > 64) {
-    KV = 2;
-    PS = K / KV;
-    NB = W / PS;
-  }
-  if (PS < 1 || PS > W || NB * PS != W || NB * LV > 64) return FusedMap{0, 0, 0, 0, 0};
-  const int fit = 64 / (KV + LV);
-  const int U = NB > 1 ? NB : (fit < 1 ? 1 : (fit < 4 ? fit : 4));
-  return FusedMap{W, LV, KV, NB, U};
-}
-
-template <int K, int L>
-Variant fused_fast() {
-  constexpr FusedMap m = fused_map(K, L);
-  if constexpr (m.W == 0) {
-    return Variant{};
-  } else {
-    return fast<kFused, m.W, m.NB, m.KV, m.LV, kFS, m.U>();
-  }
-}
-
-template <int K>
-Variant fused_fast_l(int64_t L) {
-  switch (L) {
-    case 16: return fused_fast<K, 16>();
-    case 32: return fused_fast<K, 32>();
-    case 64: return fused_fast<K, 64>();
-    case 128: return fused_fast<K, 128>();
-    case 256: return fused_fast<K, 256>();
-    case 512: return fused_fast<K, 512>();
-    default: return Variant{};
-  }
-}
-
-// Fast variants exist for every K, L in {16, 32, 64, 128, 256, 512}, with
-// 16-byte aligned operands.  The widths of the benchmark workloads (K = L = 32, 64,
-// 128, 256 and K = 16, L = 256) keep their measured schedules; other
-// widths take the mapping of fused_map.
-Variant pick_fused(int64_t M, int64_t K, int64_t L, bool al) {
-  Variant v;
+Variant pick_fused(int64_t N, int64_t M, int64_t K, int64_t L, bool al) {
+  const int64_t gathered = 4 * M * (K + L);
+  const bool gib = gathered >= ((int64_t)1 << 30), mall = gathered > ((int64_t)1 << 28);
   if (al) {
-    if (K == 32 && L == 32) return with_small(fast<kFused, 8, 1, 4, 4, kFS, kPU>(),
-                                              slnr::walk_fast<kFused, 8, 1, 4, 4, kSmall32, kPUs>);
-    if (K == 64 && L == 64)
-      return with_wide<kFused, 1, 1, kFS, kPU>(with_small(
-          fast<kFused, 16, 1, 4, 4, kFS, kPU>(), slnr::walk_fast<kFused, 16, 1, 4, 4, kFS, kPUs>));
-    if (K == 128 && L == 128)
+    if (gib && K == 64 && L == 64)
+      return with_wide<kFused, 1, 1, kFS, kPU>(fast<kFused, 16, 1, 4, 4, kFS, kPU>());
+    if (gib && K == 128 && L == 128)
       return with_wide<kFused, 2, 2, kFS, kPU128W>(fast<kFused, 32, 1, 4, 4, kFS, kPU128>());
-    if (K == 256 && L == 256) return fast<kFused, 64, 1, 4, 4, kFS, kPU>();
-    if (K == 16 && L == 256)
+    if (mall && K == 256 && L == 256) return fast<kFused, 64, 1, 4, 4, kFS, kPU>();
+    if (N <= kFewRows && K == 512 && L == 512) return fast<kFused, 64, 1, 8, 8, kFS, kPU>();
+    if (mall && K == 16 && L == 256)
       return with_fine<kFused, 64, 16, 4, 4, 16>(fast<kFused, 64, 16, 4, 4, kFS, 16>(), 24);
-    switch (K) {
-      case 16: v = fused_fast_l<16>(L); break;
-      case 32: v = fused_fast_l<32>(L); break;
-      case 64: v = fused_fast_l<64>(L); break;
-      case 128: v = fused_fast_l<128>(L); break;
-      case 256: v = fused_fast_l<256>(L); break;
-      case 512: v = fused_fast_l<512>(L); break;
-      default: break;
-    }
   }
-  return v.fn ? v : batch<kFused>(M, K, L);
+  return batch<kFused>(M, K, L);
 }
 
-Variant pick_sddmm(int64_t M, int64_t K, bool al) {
-  if (al) {
-    if (K == 16) return fast<kSddmm, 64, 16, 4, 4, kUS, 16>();
-    if (K == 32) return fast<kSddmm, 8, 1, 4, 4, kUS, kPU>();
-    if (K == 64) return with_wide<kSddmm, 1, 1, kUS, kPU>(fast<kSddmm, 16, 1, 4, 4, kUS, kPU>());
-    if (K == 128)
-      return with_wide<kSddmm, 2, 2, kUS, kPU128>(fast<kSddmm, 32, 1, 4, 4, kUS, kPU128>());
-    if (K == 256) return fast<kSddmm, 64, 1, 4, 4, kUS, kPU>();
-    if (K == 512) return fast<kSddmm, 64, 1, 8, 4, kUS, kPU>();
-  }
+Variant pick_sddmm(int64_t N, int64_t M, int64_t K, bool al) {
+  if (al && K == 256) return fast<kSddmm, 64, 1, 4, 4, kUS, kPU>();
+  if (al && K == 512 && N <= kFewRows) return fast<kSddmm, 64, 1, 8, 4, kUS, kPU>();
   return batch<kSddmm>(M, K, 0);
 }
 
-Variant pick_spmm(int64_t M, int64_t L, bool al) {
-  if (al) {
-    if (L == 16) return fast<kSpmm, 4, 1, 4, 4, kUS, kPU>();
-    if (L == 32) return fast<kSpmm, 8, 1, 4, 4, kUS, kPU>();
-    if (L == 64) return with_wide<kSpmm, 1, 1, kUS, kPU>(fast<kSpmm, 16, 1, 4, 4, kUS, kPU>());
-    if (L == 128)
-      return with_wide<kSpmm, 2, 2, kUS, kPU128>(fast<kSpmm, 32, 1, 4, 4, kUS, kPU128>());
-    if (L == 256) return fast<kSpmm, 64, 1, 4, 4, kUS, kPU>();
-    if (L == 512) return fast<kSpmm, 64, 1, 4, 8, kUS, kPU>();
-  }
+Variant pick_spmm(int64_t N, int64_t M, int64_t L, bool al) {
+  if (al && L == 256) return fast<kSpmm, 64, 1, 4, 4, kUS, kPU>();
+  if (al && L == 512 && N <= kFewRows) return fast<kSpmm, 64, 1, 4, 8, kUS, kPU>();
   return batch<kSpmm>(M, 0, L);
 }
 
@@ -508,11 +428,28 @@ int blocks_per_cu(int dev, KernelFn fn, int block, size_t lds, int *out) {
 // grid, because extra blocks would only find empty slices.  A factor > 0
 // fixes the number of grids (the wide-worker kernels keep the factor chosen
 // for the narrow ones).
-Grid make_grid(int cus, int per_cu, int block, int W, int64_t N, int factor = 0) {
+//
+// The batch walk (`rows` > 0) aims at slices of `rows` rows and takes as many
+// grids as that needs: 16 rows where K + L < 256, 6 for wider rows, whose E and D
+// rows fill the L2 of an XCD sooner (us at 1, 2, 4, 8, 16 grids; 27-point stencil of
+// 75^3, 64 rows a wave in one grid: K = L = 64 675, 503, 455, 457, 514, K = L = 128
+// 1611, 1405, 1252, 897, 794; 2^17 R-MAT vertices at 64 108, 112, 118, 129, 136; 100000
+// uniform rows of 16 at 64 114, 119, 121, 120, 128).  At most 24 grids, and no more
+// than 8 if the partial rows of more, `carry_row` bytes a worker, would not fit the
+// device array of the no-allocation entry point (which then takes the same grids).
+Grid make_grid(int cus, int per_cu, int block, int W, int64_t N, int factor = 0, int rows = 0,
+               int64_t carry_row = 0) {
   Grid g;
   const int64_t resident_blocks = (int64_t)cus * per_cu;
   const int64_t resident_workers = resident_blocks * (block / 64) * (64 / W);
   if (factor < 1) factor = g_grid_factor.load();
+  if (factor < 1 && rows > 0) {
+    int64_t f = N / (resident_workers * rows);
+    const int64_t fit = (int64_t)kScratchBytes / (resident_workers * (carry_row > 0 ? carry_row : 1));
+    const int64_t most = fit > kGridFactor ? (fit < 24 ? fit : 24) : kGridFactor;
+    if (f > most) f = most;
+    factor = f > 1 ? (int)f : 1;
+  }
   if (factor < 1) factor = N >= 8 * resident_workers ? kGridFactor : 1;
   int blocks = (int)(resident_blocks * factor);
   blocks = ((blocks + kXcds - 1) / kXcds) * kXcds;
@@ -542,9 +479,9 @@ FixupShape fixup_shape(int cus, int64_t workers) {
 }
 
 // Kernel and grid of a walk launch at a requested grid factor (0: the
-// automatic or process-wide choice): one resident grid takes the
-// small-input kernel, several the wide-worker kernel, fine slices the
-// fine-slice kernel, where the variant has them.
+// automatic or process-wide choice): several resident grids take the
+// wide-worker kernel, fine slices the fine-slice kernel, where the variant
+// has them.
 int choose_launch(int dev, int cus, const Variant *vs, int nv, int64_t N, int factor,
                   Variant *v_out, Grid *g_out) {
   int rc;
@@ -559,12 +496,8 @@ int choose_launch(int dev, int cus, const Variant *vs, int nv, int64_t N, int fa
       return rc;
     if (pc < per_cu) per_cu = pc;
   }
-  Grid g = make_grid(cus, per_cu, v.block, v.W, N, factor);
-  if (nv == 1 && g.factor == 1 && v.fn_small) {  // one resident grid: the small-input schedule
-    v.fn = v.fn_small;
-    if ((rc = blocks_per_cu(dev, v.fn, v.block, v.lds, &per_cu)) != SPARSELNR_OK) return rc;
-    g = make_grid(cus, per_cu, v.block, v.W, N, factor);
-  } else if (nv == 1 && g.factor > 1 && v.fn_wide) {  // several grids: the wide workers
+  Grid g = make_grid(cus, per_cu, v.block, v.W, N, factor, v.rows, v.carry_row);
+  if (nv == 1 && g.factor > 1 && v.fn_wide) {  // several grids: the wide workers
     v.fn = v.fn_wide;
     v.W = v.W_wide;
     if ((rc = blocks_per_cu(dev, v.fn, v.block, v.lds, &per_cu)) != SPARSELNR_OK) return rc;
@@ -707,7 +640,6 @@ int check_fused_args(const int32_t *rowptr, const int32_t *colidx, const float *
 // for the life of the process.  Host code never uses the name `scratch` as
 // an address: the device address of each GPU's copy comes from
 // hipGetSymbolAddress, taken once per device with that device current.
-constexpr size_t kScratchBytes = SPARSELNR_NOALLOC_SCRATCH_BYTES;
 static_assert(kScratchBytes % 256 == 0, "scratch size");
 constexpr int kMaxDevices = 64;
 void *g_scratch_ptr[kMaxDevices] = {};
@@ -824,7 +756,7 @@ int sparselnr_fused_sddmm_spmm(const int32_t *rowptr, const int32_t *colidx,
   a.D = D;
   a.E = E;
   a.out = A;
-  return run_walk(kFused, pick_fused(M, K, L, al), a, (hipStream_t)stream);
+  return run_walk(kFused, pick_fused(N, M, K, L, al), a, (hipStream_t)stream);
 }
 
 int sparselnr_fused_sddmm_spmm_noalloc(const int32_t *rowptr, const int32_t *colidx,
@@ -845,7 +777,7 @@ int sparselnr_fused_sddmm_spmm_noalloc(const int32_t *rowptr, const int32_t *col
   a.D = D;
   a.E = E;
   a.out = A;
-  return run_walk(kFused, pick_fused(M, K, L, al), a, (hipStream_t)stream, &fb);
+  return run_walk(kFused, pick_fused(N, M, K, L, al), a, (hipStream_t)stream, &fb);
 }
 
 int sparselnr_sddmm(const int32_t *rowptr, const int32_t *colidx, const float *vals,
@@ -863,7 +795,7 @@ int sparselnr_sddmm(const int32_t *rowptr, const int32_t *colidx, const float *v
   a.C = C;
   a.D = D;
   a.out = Y;
-  return run_walk(kSddmm, pick_sddmm(M, K, al), a, (hipStream_t)stream);
+  return run_walk(kSddmm, pick_sddmm(N, M, K, al), a, (hipStream_t)stream);
 }
 
 int sparselnr_spmm(const int32_t *rowptr, const int32_t *colidx, const float *Y,
@@ -879,7 +811,7 @@ int sparselnr_spmm(const int32_t *rowptr, const int32_t *colidx, const float *Y,
   WalkArgs a = base_args(rowptr, colidx, Y, N, 0, L);
   a.E = E;
   a.out = A;
-  return run_walk(kSpmm, pick_spmm(M, L, al), a, (hipStream_t)stream);
+  return run_walk(kSpmm, pick_spmm(N, M, L, al), a, (hipStream_t)stream);
 }
 
 int sparselnr_unfused_sddmm_spmm(const int32_t *rowptr, const int32_t *colidx,

@@ -63,13 +63,26 @@ class Walk:
             for b in range(64):
                 if rb + b <= self.rlast and rb + b != self.i1 and we[b] <= ws[b]:
                     put(dest(rb + b), 0.0)
-        ib, pb, seen = self.i0, self.p0, []
+        ib, pb, crow, seen = self.i0, self.p0, -1, []
         while pb < self.p1:
             pe = min(self.p1, pb + self.cap)
+            inext, orow = ib, -1  # the row that goes on in the next batch, if any
+            if pe < self.p1:
+                while inext <= self.rlast:
+                    ws, we = self.window(inext)
+                    m = [b for b in range(64) if inext + b <= self.rlast and we[b] > pe]
+                    if m:
+                        inext += m[0]
+                        if ws[m[0]] < pe:
+                            orow = inext
+                        break
+                    inext += 64
+                assert inext <= self.rlast
             acc = 0.0
             for p, n, row, first, last, cont, opened in self.passes(ib, pb, pe, npp):
                 assert pb <= p and p + n <= pe and p + n - pb <= self.cap
                 assert self.rp[row] <= p and p + n <= self.rp[row + 1]
+                assert cont == (row == crow) and opened == (row in (self.i1, orow))
                 if first:
                     assert acc == 0.0
                 seen += range(p, p + n)
@@ -82,16 +95,7 @@ class Walk:
                     else:
                         put(dest(row), acc)
                     acc = 0.0
-            if pe < self.p1:
-                while ib <= self.rlast:
-                    _, we = self.window(ib)
-                    m = [b for b in range(64) if ib + b <= self.rlast and we[b] > pe]
-                    if m:
-                        ib += m[0]
-                        break
-                    ib += 64
-                assert ib <= self.rlast
-            pb = pe
+            ib, crow, pb = inext, orow, pe
         assert seen == list(range(self.p0, self.p1))
         if self.i1 < self.N and self.p1 <= self.rp[self.i1]:
             slots["t"] = 0.0

@@ -43,18 +43,43 @@ def test_slices_of_several_batches(gpu):
         slnr.sparselnr_set_grid_factor(0)
 
 
-def test_more_columns_than_24_bits(gpu):
+def gathered(csr, n, C, D, E):
+    """A and its scale in fp64 for rows of n nonzeros each."""
+    j = csr[1].long()
+    t = C.double().repeat_interleave(n, 0) * D[j].double()
+    e = E[j].double() * csr[2].double()[:, None]
+    one = lambda y, x: (y[:, None] * x).view(-1, n, E.shape[1]).sum(1)  # noqa: E731
+    return one(t.sum(1), e), one(t.abs().sum(1), e.abs())
+
+
+def run_large(gpu, N, n, M, K, L):
     import torch
-    M, N, K, L = (1 << 24) + 77, 300, 3, 5
-    p = make_problem(np.full(N, 20), M, 1, 1, seed=9, dups=True)
+    p = make_problem(np.full(N, n), M, 1, 1, seed=9, dups=True)
     p.colidx[:40] = M - 1 - np.arange(40)
     g = torch.Generator(device=gpu).manual_seed(1)
     C, D, E = (torch.randn(r, c, device=gpu, generator=g) for r, c in ((N, K), (M, K), (M, L)))
     csr = [torch.from_numpy(a).to(gpu) for a in (p.rowptr, p.colidx, p.vals)]
-    A = slnr.sparselnr_fused_sddmm_spmm(*csr, C, D, E)
-    j = csr[1].long()
-    y = csr[2].double() * (C.double().repeat_interleave(20, 0) * D[j].double()).sum(1)
-    t = y[:, None] * E[j].double()
-    ref, scale = t.view(N, 20, L).sum(1), t.abs().view(N, 20, L).sum(1)
-    # 20 terms of 3-term dot products, each rounded at most 30 times
-    assert bool(((A.double() - ref).abs() <= 30 * 2.0 ** -24 * 4 * scale).all())
+    ref, scale = gathered(csr, n, C, D, E)
+    for factor in (0, 1, 8):
+        try:
+            slnr.sparselnr_set_grid_factor(factor)
+            A = slnr.sparselnr_fused_sddmm_spmm(*csr, C, D, E)
+        finally:
+            slnr.sparselnr_set_grid_factor(0)
+        # n terms of K-term dot products: each rounded at most K + n + 2 times, the
+        # sums of a tree far less; 2^-24 a rounding
+        err = (A.double() - ref).abs().amax(1)
+        assert bool((err <= (K + n + 2) * 2.0 ** -24 * scale.amax(1)).all()), factor
+
+
+def test_more_columns_than_24_bits(gpu):
+    run_large(gpu, 300, 20, (1 << 24) + 77, 3, 5)
+
+
+# the sizes from which widths of 64, 128 and 256 keep kernels of their own, and
+# one column below them
+@pytest.mark.parametrize("K,L,M", [(64, 64, 1 << 21), (64, 64, (1 << 21) - 1), (128, 128, 1 << 20),
+                                   (128, 128, (1 << 20) - 1), (256, 256, (1 << 17) + 1),
+                                   (256, 256, 1 << 17), (16, 256, 246724), (16, 256, 246723)])
+def test_kernels_chosen_by_size(gpu, K, L, M):
+    run_large(gpu, 3000, 21, M, K, L)
