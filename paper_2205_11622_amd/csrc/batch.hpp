@@ -23,6 +23,8 @@
 //     27-point stencil of 101^3 at K = L = 64: 1815 -> 1020
 //   whose groups wait for the longest row among them, and whose burst of one row
 //   ends before the next begins.
+// Where neighbouring rows share columns, the fabric is spared by few rows being
+// walked at a time: slices of wide rows are shared by several waves (make_part).
 #pragma once
 
 #include "walker.hpp"
@@ -137,15 +139,79 @@ __device__ __forceinline__ void ld_cols(float (&r)[4], const float *base, int j,
   }
 }
 
+// Parts of a slice of S items: `most` (odd), or the odd number that leaves about
+// kPartItems to each.  A part costs 5 to 7 us of its wave's time in searches and
+// first loads.  us at parts of 80 / 64 items and at whole slices: 1M uniform rows of
+// 16 at K = L = 128 2870 / 2915 / 2744, SpMM at 256 with 1M rows of 4 918 / 1024 / 840.
+constexpr uint32_t kPartItems = 80;
+
+__device__ __forceinline__ uint32_t parts_of(int64_t S, int most) {
+  if (S >= (int64_t)most * kPartItems) return (uint32_t)most;
+  const uint32_t fit = (uint32_t)S / kPartItems;
+  return fit > 1 ? fit | 1 : 1;
+}
+
+// One wave's share of a slice: part q of its parts.
+struct Part {
+  int64_t id;              // slice, and its carry slots
+  int64_t i0, p0, i1, p1;  // start and end coordinates
+  bool head;               // row i0 began in an earlier slice and ends here
+  bool first, last;        // part of the slice
+  int head_row;            // of the first part: the slice's head row or -1
+  bool active;
+};
+
+// A slice is walked in up to a.parts parts of equal length whose inner cuts move back
+// to the start of their row (of a row begun in an earlier slice: to the slice's start),
+// so a part needs no carry slot.  What a slice holds of a row that goes on after it
+// falls to its last part, and of a row that began before it to the part in which
+// that row ends.  Part q of slice s comes right before part q + 1 on an XCD.
+__device__ __forceinline__ Part make_part(const WalkArgs &a) {
+  Part s;
+  int64_t S, ns, items, nnz;
+  slice_count(a, &S, &ns, &items, &nnz);
+  const int64_t per_xcd = (ns + a.xcds - 1) / a.xcds;
+  const uint32_t in_xcd = blockIdx.x / (uint32_t)a.xcds;
+  const uint32_t parts = parts_of(S, a.parts);
+  const uint32_t slice = in_xcd / parts, q = in_xcd % parts;
+  s.id = (int64_t)(blockIdx.x % (uint32_t)a.xcds) * per_xcd + slice;
+  s.active = slice < per_xcd && s.id < ns;
+  s.first = q == 0;
+  s.last = q + 1 == parts;
+  s.head = false;
+  s.head_row = -1;
+  s.i0 = s.p0 = s.i1 = s.p1 = 0;
+  if (!s.active) return s;
+  const int64_t d0 = s.id * S;
+  const int64_t d1 = d0 + S < items ? d0 + S : items;
+  const int64_t da = d0 + S * q / parts, db = d0 + S * (q + 1) / parts;
+  mp_search2<64>(a.rowptr, a.N, nnz, da < d1 ? da : d1, db < d1 ? db : d1, &s.i0, &s.i1);
+  // Row i at the start of its nonzeros, or where the slice boundary `d` cuts it:
+  // boundaries split rows of more than `snap` nonzeros only (as in make_slice).
+  const int64_t snap = snap_length(S);
+  auto at = [&](int64_t i, int64_t d) {
+    if (i >= a.N) return nnz;
+    const int64_t r0 = a.rowptr[i], r1 = a.rowptr[i + 1];
+    return r0 + i < d && r1 - r0 > snap ? d - i : r0;
+  };
+  s.p0 = at(s.i0, d0);
+  s.p1 = at(s.i1, s.last ? d1 : d0);
+  if (s.i0 < a.N && s.p0 > (int64_t)a.rowptr[s.i0]) {
+    s.head = s.i0 < s.i1;
+    if ((int64_t)a.rowptr[s.i0 + 1] + s.i0 + 1 <= d1) s.head_row = (int)s.i0;
+  }
+  return s;
+}
+
 // TAIL: K or L is no multiple of 4.  BIG: 64-bit row offsets.
 template <int MODE, bool TAIL, bool BIG>
 struct BatchWalk {
   const WalkArgs &a;
   int2 *nz;
   int lane;
-  int i0, p0, i1, p1;  // the slice
+  int i0, p0, i1, p1;  // the part
   bool head;
-  int rlast;           // last row with a segment in the slice
+  int rlast;           // last row with a segment in the part
   float *head_slot, *tail_slot;
   int wrb;             // rowptr window: row wrb + lane covers ws .. we of the slice
   int ws, we;
@@ -296,11 +362,17 @@ struct BatchWalk {
         });
   }
 
+  // Where the sums of a row go (column l0 of it), also those of a first batch of it.
+  __device__ __forceinline__ float *row_at(int row) const {
+    return row == i1           ? tail_slot
+           : row == i0 && head ? head_slot
+                               : a.out + (int64_t)row * a.L + a.l0;
+  }
+
   // Columns l0 + [4 * q0, 4 * q0 + 4 * nq) of the rows of the batch.  crow: the
-  // row begun in an earlier batch of the slice, orow: the one that goes on in
-  // a later batch (-1: none).
+  // row begun in an earlier batch of the part (-1: none).
   template <int G>
-  __device__ __forceinline__ void rows(int ib, int pb, int pe, int q0, int nq, int crow, int orow) {
+  __device__ __forceinline__ void rows(int ib, int pb, int pe, int q0, int nq, int crow) {
     constexpr int NPP = 64 / G, U = 4;
     int ln = lane;
     asm volatile("" : "+v"(ln));
@@ -362,15 +434,13 @@ struct BatchWalk {
 #pragma unroll
           for (int v = 0; v < 4; ++v) acc[v] = groups_sum<G>(acc[v]);
           if (lane_in && g == 0) {
+            float *dst = row_at(row) + col;
             if (row == crow) {
 #pragma unroll
               for (int v = 0; v < 4; ++v)
-                if (!TAIL || v < valid || a.Lw >= 4) acc[v] = tail_slot[col + v] + acc[v];
+                if (!TAIL || v < valid || a.Lw >= 4) acc[v] = dst[v] + acc[v];
             }
-            store(row == i1 || row == orow ? tail_slot + col
-                  : row == i0 && head      ? head_slot + col
-                                           : a.out + (int64_t)row * a.L + a.l0 + col,
-                  acc);
+            store(dst, acc);
           }
         },
         [&](auto r, int rb, i4_t b, i4_t s, i4_t e) {
@@ -395,15 +465,13 @@ struct BatchWalk {
             int row = rb + (k == 0 ? b.x : b.y);
             if constexpr (R == 4) row = k < 2 ? row : rb + (k == 2 ? b.z : b.w);
             if (lane_in && (ln & (64 / R - 1)) < G) {
+              float *dst = row_at(row) + col;
               if (row == crow) {
 #pragma unroll
                 for (int v = 0; v < 4; ++v)
-                  if (!TAIL || v < valid || a.Lw >= 4) o[v] = tail_slot[col + v] + o[v];
+                  if (!TAIL || v < valid || a.Lw >= 4) o[v] = dst[v] + o[v];
               }
-              store(row == i1 || row == orow ? tail_slot + col
-                    : row == i0 && head      ? head_slot + col
-                                             : a.out + (int64_t)row * a.L + a.l0 + col,
-                    o);
+              store(dst, o);
             }
           }
         });
@@ -417,13 +485,13 @@ struct BatchWalk {
       while (m) {
         const int row = rb + __builtin_ctzll(m);
         m &= m - 1;
-        float *dst = row == i0 && head ? head_slot : a.out + (int64_t)row * a.L + a.l0;
+        float *dst = row_at(row);
         for (int l = lane; l < a.Lw; l += 64) __builtin_nontemporal_store(0.f, dst + l);
       }
     }
   }
 
-  __device__ __forceinline__ void run(const Slice &s) {
+  __device__ __forceinline__ void run(const Part &s) {
     lane = threadIdx.x & 63;
     i0 = __builtin_amdgcn_readfirstlane((int)s.i0);
     p0 = __builtin_amdgcn_readfirstlane((int)s.p0);
@@ -493,26 +561,24 @@ struct BatchWalk {
         const int q4 = (a.Lw + 3) >> 2;
         for (int q0 = 0; q0 < q4; q0 += a.tl) {
           const int nq = q4 - q0 < a.tl ? q4 - q0 : a.tl;
-          if (nq <= 4) rows<4>(ib, pb, pe, q0, nq, crow, orow);
-          else if (nq <= 8) rows<8>(ib, pb, pe, q0, nq, crow, orow);
-          else if (nq <= 16) rows<16>(ib, pb, pe, q0, nq, crow, orow);
-          else if (nq <= 32) rows<32>(ib, pb, pe, q0, nq, crow, orow);
-          else rows<64>(ib, pb, pe, q0, nq, crow, orow);
+          if (nq <= 4) rows<4>(ib, pb, pe, q0, nq, crow);
+          else if (nq <= 8) rows<8>(ib, pb, pe, q0, nq, crow);
+          else if (nq <= 16) rows<16>(ib, pb, pe, q0, nq, crow);
+          else if (nq <= 32) rows<32>(ib, pb, pe, q0, nq, crow);
+          else rows<64>(ib, pb, pe, q0, nq, crow);
         }
       }
       ib = inext;
       crow = orow;
       pb = pe;
     }
-    // A tail segment without a nonzero: its slot may hold a row carried from
-    // one batch to the next, so it is cleared last.
-    if (MODE != kSddmm && i1 < a.N && p1 <= a.rowptr[i1]) {
+    if (MODE != kSddmm && s.last && i1 < a.N && p1 <= a.rowptr[i1]) {  // an empty tail
       for (int l = lane; l < a.Lw; l += 64) tail_slot[l] = 0.f;
     }
     if (MODE != kSddmm && lane == 0) {
       int32_t *meta = a.meta + 2 * (int64_t)id;
-      meta[0] = i1 < a.N ? i1 : -1;
-      meta[1] = head ? i0 : -1;
+      if (s.last) meta[0] = i1 < a.N ? i1 : -1;
+      if (s.first) meta[1] = s.head_row;
     }
   }
 };
@@ -522,7 +588,7 @@ struct BatchWalk {
 template <int MODE, bool TAIL, bool BIG>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(6))) void walk_batch(WalkArgs a) {
   __shared__ int2 nonzeros[kBatch];
-  const Slice s = make_slice<64>(a);
+  const Part s = make_part(a);
   if (!s.active) return;
   BatchWalk<MODE, TAIL, BIG> w(a, nonzeros);
   w.run(s);

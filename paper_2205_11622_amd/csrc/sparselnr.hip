@@ -32,6 +32,7 @@ constexpr int kMinChunk = 64;     // smallest merge-path slice per worker (see s
 constexpr int kXcds = 8;          // MI355X deals blocks over 8 XCDs
 constexpr int kGridFactor = 8;    // resident grids per walk launch for large inputs
 constexpr int kBatchTile = 64;    // batch walk: at most 64 float4 columns per tile
+constexpr int kMaxParts = 31;     // batch walk: at most 31 parts of a slice
 constexpr size_t kScratchBytes = SPARSELNR_NOALLOC_SCRATCH_BYTES;  // no-allocation device array
 constexpr int kBatchL = 512;      // batch walk: at most 512 columns of A per launch
 // <SpMMH, GEMM>: C .* D is formed once when nnz >= kHoistRatio * M (12 M J
@@ -156,11 +157,10 @@ struct Variant {
   int block = kBlock;  // threads per block
   KernelFn fn_wide = nullptr;   // wider workers, for inputs that need several resident grids
   int W_wide = 64;
-  KernelFn fn_fine = nullptr;   // same mapping, for grids of at least fine_factor resident grids
-  int fine_factor = 0;
   int tk = 1, tl = 1;  // batch walk: float4 columns of a tile
   int rows = 0;        // batch walk: rows per slice that the automatic grid aims at
   int64_t carry_row = 0;  // and bytes of carry per worker
+  int part_rows = 0;      // rows per part of a slice (0: slices are not parted)
 };
 
 template <int MODE, int W, int NB, int KV, int LV, int SCHED = slnr::kPipelined, int U = 1>
@@ -225,14 +225,14 @@ Variant batch(int64_t M, int64_t K, int64_t L) {
   v.tk = batch_tile(K);
   v.tl = batch_tile(L < kBatchL ? L : kBatchL);
   v.rows = K + L < 256 ? 16 : 6;
+  v.part_rows = K + L >= 256 ? 3 : K >= 96 || L >= 96 ? 6 : 0;
   v.carry_row = MODE == kSddmm ? 0 : 2 * (L < kBatchL ? L : kBatchL) * 4 + 8;
   return v;
 }
 
 // Gather schedule of the fixed-width fused kernels and of the unfused (SDDMM,
 // SpMM) ones, each set to what measured fastest for it on MI355X: the fused
-// kernels pace their gathers (the K = 16, L = 256 one only for coarse slices,
-// see with_fine), the unfused ones pipeline them.  Nonzeros per
+// kernels pace their gathers, the unfused ones pipeline them.  Nonzeros per
 // step of the paced schedule: 8 for the 128-wide rows, 4 otherwise (the
 // 64-lane kernels of large inputs take their own, below).
 constexpr int kFS = slnr::kPaced;
@@ -259,25 +259,6 @@ Variant with_wide(Variant v) {
   return v;
 }
 
-// Fine slices (many resident grids per launch) take the pipelined schedule.
-// Measured on MI355X, the fused kernel at K = 16, L = 256 on the 27-point
-// stencil of a 128^3 grid (2^21 rows), ms per call by resident grids:
-//             8     12     24     48     64
-//   paced   5.85  5.77   5.79   5.80   6.02
-//   piped   6.61  6.10   5.61   5.04   5.09
-// With fine slices the rows walked at one moment on an XCD lie close
-// together and their E rows come back from the caches; the pipelined walk
-// holds 56 fewer registers of gathered rows than the 16-nonzero paced step,
-// so more waves share the CU and more gathers are in flight.  With coarse
-// slices the gathers go further out and the paced walk, which keeps fewer
-// in flight per wave, is faster.
-template <int MODE, int W, int NB, int KV, int LV, int U>
-Variant with_fine(Variant v, int from) {
-  v.fn_fine = slnr::walk_fast<MODE, W, NB, KV, LV, slnr::kPipelined, U>;
-  v.fine_factor = from;
-  return v;
-}
-
 // The batch walk serves every width; the kernels of fixed width stay where they
 // are the faster ones (us on MI355X, fixed width / batch):
 //  * K = L = 64 and 128 with at least 1 GiB of D and E rows, 64-lane workers.
@@ -287,40 +268,35 @@ Variant with_fine(Variant v, int from) {
 //    matrices of that size lose by it: 3M uniform rows of 16 at 64 5296 / 4491.)
 //    Below 1 GiB the batch walk is ahead on all: 2^19 vertices at 64 598 / 479, 2^18
 //    at 128 582 / 520, 700001 power-law rows at 128 2508 / 2010.
-//  * K = L = 256 and K = 16, L = 256 with more than 256 MiB of them (the size of
-//    the memory-side cache): 27-point stencil of 101^3 at 256 6609 / 7196; below
-//    it 36^3 at 256 212 / 175.
-//  * SDDMM at K = 256 and SpMM at L = 256: stencil of 36^3 84 / 96, 82 / 87;
-//    elsewhere within 2%.
 //  * widths of 512 (two tiles of the batch walk, one after the other) with few
 //    rows a wave: 3000 power-law rows of 20 at K = L = 512 54 / 63, 2^13 R-MAT
 //    vertices SDDMM 24 / 36; 46656 rows 487 / 408.
+// At K = L = 256, K = 16 with L = 256 and 256 alone the parts of the batch walk's
+// slices (make_grid) put it ahead: 27-point stencil of 101^3 at K = L = 256
+// 6100 / 4055, of 128^3 at 16, 256 5883 / 4740, SpMM at 256 of 101^3 3200 / 2163, of
+// 36^3 84 / 75; R-MAT and power-law graphs within 1%; rows of 3 or 4 nonzeros, which
+// have no use for parts, SpMM at 256 839 / 918 and SDDMM 703 / 737.
 constexpr int64_t kFewRows = 16384;
 
 Variant pick_fused(int64_t N, int64_t M, int64_t K, int64_t L, bool al) {
   const int64_t gathered = 4 * M * (K + L);
-  const bool gib = gathered >= ((int64_t)1 << 30), mall = gathered > ((int64_t)1 << 28);
+  const bool gib = gathered >= ((int64_t)1 << 30);
   if (al) {
     if (gib && K == 64 && L == 64)
       return with_wide<kFused, 1, 1, kFS, kPU>(fast<kFused, 16, 1, 4, 4, kFS, kPU>());
     if (gib && K == 128 && L == 128)
       return with_wide<kFused, 2, 2, kFS, kPU128W>(fast<kFused, 32, 1, 4, 4, kFS, kPU128>());
-    if (mall && K == 256 && L == 256) return fast<kFused, 64, 1, 4, 4, kFS, kPU>();
     if (N <= kFewRows && K == 512 && L == 512) return fast<kFused, 64, 1, 8, 8, kFS, kPU>();
-    if (mall && K == 16 && L == 256)
-      return with_fine<kFused, 64, 16, 4, 4, 16>(fast<kFused, 64, 16, 4, 4, kFS, 16>(), 24);
   }
   return batch<kFused>(M, K, L);
 }
 
 Variant pick_sddmm(int64_t N, int64_t M, int64_t K, bool al) {
-  if (al && K == 256) return fast<kSddmm, 64, 1, 4, 4, kUS, kPU>();
   if (al && K == 512 && N <= kFewRows) return fast<kSddmm, 64, 1, 8, 4, kUS, kPU>();
   return batch<kSddmm>(M, K, 0);
 }
 
 Variant pick_spmm(int64_t N, int64_t M, int64_t L, bool al) {
-  if (al && L == 256) return fast<kSpmm, 64, 1, 4, 4, kUS, kPU>();
   if (al && L == 512 && N <= kFewRows) return fast<kSpmm, 64, 1, 4, 8, kUS, kPU>();
   return batch<kSpmm>(M, 0, L);
 }
@@ -394,6 +370,7 @@ struct Grid {
   int workers;
   int xcd_span;
   int factor;
+  int parts;  // waves that share a slice (batch walk)
 };
 
 // Resident blocks per CU for `fn` (occupancy query, cached per device).
@@ -437,8 +414,20 @@ int blocks_per_cu(int dev, KernelFn fn, int block, size_t lds, int *out) {
 // uniform rows of 16 at 64 114, 119, 121, 120, 128).  At most 24 grids, and no more
 // than 8 if the partial rows of more, `carry_row` bytes a worker, would not fit the
 // device array of the no-allocation entry point (which then takes the same grids).
+//
+// Wide rows (`part_rows` > 0) are walked by several waves a slice, each a part of it
+// (make_part): the rows that the waves of an XCD walk at one moment are then so few
+// that the D and E rows which neighbouring rows share stay in its 4 MB of L2, and the
+// parts need no carry.  Parts of 3 rows from 256 floats a nonzero on, of 6 where one
+// of the two rows has 96 (us, whole slices / parts, 27-point stencils: K = L = 128 of
+// 101^3 2757 / 2040, SpMM at 128 1854 / 1015, K = 16, L = 256 of 128^3 6441 / 4740);
+// narrower rows fit as they are (K = L = 64 of 101^3 1066 / 1134).  The device makes
+// fewer of them where rows are short (kPartItems); the waves left over end at once,
+// at 4.5 a ns: 1M uniform rows of 4 at K = L = 128 920 / 968, of 16 2744 / 2870.  The number is odd: with 2, 4 or 8
+// parts the last one of each slice, which has the ends of long rows, would always
+// meet the same shader engines (2^19 R-MAT vertices at 64: 4 parts 847, 5 514).
 Grid make_grid(int cus, int per_cu, int block, int W, int64_t N, int factor = 0, int rows = 0,
-               int64_t carry_row = 0) {
+               int64_t carry_row = 0, int part_rows = 0) {
   Grid g;
   const int64_t resident_blocks = (int64_t)cus * per_cu;
   const int64_t resident_workers = resident_blocks * (block / 64) * (64 / W);
@@ -457,6 +446,12 @@ Grid make_grid(int cus, int per_cu, int block, int W, int64_t N, int factor = 0,
   g.workers = blocks * (block / 64) * (64 / W);
   g.xcd_span = blocks / kXcds;  // XCD-contiguous slice numbering
   g.factor = factor;
+  g.parts = 1;
+  if (part_rows > 0 && g_grid_factor.load() < 1) {
+    const int64_t q = N / ((int64_t)g.workers * part_rows);
+    g.parts = q < 2 ? 1 : q < kMaxParts ? (int)q | 1 : kMaxParts;
+    g.blocks *= g.parts;
+  }
   return g;
 }
 
@@ -480,8 +475,7 @@ FixupShape fixup_shape(int cus, int64_t workers) {
 
 // Kernel and grid of a walk launch at a requested grid factor (0: the
 // automatic or process-wide choice): several resident grids take the
-// wide-worker kernel, fine slices the fine-slice kernel, where the variant
-// has them.
+// wide-worker kernel, where the variant has one.
 int choose_launch(int dev, int cus, const Variant *vs, int nv, int64_t N, int factor,
                   Variant *v_out, Grid *g_out) {
   int rc;
@@ -496,14 +490,10 @@ int choose_launch(int dev, int cus, const Variant *vs, int nv, int64_t N, int fa
       return rc;
     if (pc < per_cu) per_cu = pc;
   }
-  Grid g = make_grid(cus, per_cu, v.block, v.W, N, factor, v.rows, v.carry_row);
+  Grid g = make_grid(cus, per_cu, v.block, v.W, N, factor, v.rows, v.carry_row, v.part_rows);
   if (nv == 1 && g.factor > 1 && v.fn_wide) {  // several grids: the wide workers
     v.fn = v.fn_wide;
     v.W = v.W_wide;
-    if ((rc = blocks_per_cu(dev, v.fn, v.block, v.lds, &per_cu)) != SPARSELNR_OK) return rc;
-    g = make_grid(cus, per_cu, v.block, v.W, N, g.factor);
-  } else if (nv == 1 && v.fn_fine && g.factor >= v.fine_factor) {  // fine slices
-    v.fn = v.fn_fine;
     if ((rc = blocks_per_cu(dev, v.fn, v.block, v.lds, &per_cu)) != SPARSELNR_OK) return rc;
     g = make_grid(cus, per_cu, v.block, v.W, N, g.factor);
   }
@@ -562,6 +552,7 @@ int run_walk(Mode mode, const Variant *vs, const WalkArgs *as, int nv, hipStream
   a.xcds = kXcds;
   a.tk = v.tk;
   a.tl = v.tl;
+  a.parts = g.parts;
   if (mode != kSddmm) {
     const CarrySize cs = carry_size(g, tile_w);
     void *ws = nullptr;
@@ -591,6 +582,7 @@ int run_walk(Mode mode, const Variant *vs, const WalkArgs *as, int nv, hipStream
       ak.Lw = a.Lw;
       ak.tk = a.tk;
       ak.tl = a.tl;
+      ak.parts = a.parts;
       const Variant &vk = k == 0 ? v : vs[k];  // v: the kernel chosen for this input
       hipLaunchKernelGGL(vk.fn, dim3(g.blocks), dim3(vk.block), vk.lds, stream, ak);
       hipError_t e = hipGetLastError();

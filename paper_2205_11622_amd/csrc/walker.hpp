@@ -88,6 +88,7 @@ struct WalkArgs {
   int64_t gate_nnz;
   int32_t gate;
   int32_t tk, tl;     // batch walk: float4 columns of a tile of C / D and of E / A
+  int32_t parts;      // batch walk: waves for a slice (odd)
 };
 
 enum Gate : int { kGateNone = 0, kGateDense = 1, kGateSparse = 2 };
@@ -315,6 +316,12 @@ __device__ __forceinline__ void slice_count(const WalkArgs &a, int64_t *S_out, i
   *nnz_out = nnz;
 }
 
+// Longest row that no boundary of slices of S items splits.
+__device__ __forceinline__ int64_t snap_length(int64_t S) {
+  const int64_t snap_short = S < kSnapRow ? S : kSnapRow;
+  return S / 4 > snap_short ? S / 4 : snap_short;
+}
+
 template <int W>
 __device__ __forceinline__ Slice make_slice(const WalkArgs &a) {
   Slice s;
@@ -348,8 +355,7 @@ __device__ __forceinline__ Slice make_slice(const WalkArgs &a) {
   // leave no partial rows to the fixup.  Both slices sharing the boundary
   // apply the same rule, and the rule is monotone, so slices stay contiguous
   // and ordered; snap never exceeds S, so no slice is left empty by it.
-  const int64_t snap_short = S < kSnapRow ? S : kSnapRow;
-  const int64_t snap = S / 4 > snap_short ? S / 4 : snap_short;
+  const int64_t snap = snap_length(S);
   auto snap_back = [&](int64_t i, int64_t &p) {
     if (i < a.N) {
       const int64_t r0 = a.rowptr[i];

@@ -1,8 +1,8 @@
-"""Host model of the batch walk (csrc/batch.hpp): the batches of a
-slice, the rowptr windows and the passes over row segments, re-enacted on many
-CSR shapes.  Every nonzero of a slice is passed once, in a pass of its own
-row; every row end is written exactly once, partial rows go through the
-slice's own slots, and every index stays inside its array."""
+"""Host model of the batch walk (csrc/batch.hpp): the parts of a slice, their
+batches, the rowptr windows and the passes over row segments, re-enacted on many
+CSR shapes.  Every nonzero of a part is passed once, in a pass of its own row;
+every row end is written exactly once, partial rows go through the slice's own
+slots, each of them written by one part, and every index stays inside its array."""
 import numpy as np
 import pytest
 
@@ -10,9 +10,9 @@ from tests.test_partition import slice_bounds, slice_len, snap_len
 
 
 class Walk:
-    def __init__(self, rowptr, N, i0, p0, i1, p1, cap):
+    def __init__(self, rowptr, N, i0, p0, i1, p1, cap, last=True):
         self.rp, self.N, self.i0, self.p0, self.i1, self.p1 = rowptr, N, i0, p0, i1, p1
-        self.cap = cap
+        self.cap, self.last = cap, last
         self.head = i0 < i1 and p0 > rowptr[i0]
         self.rlast = i1 if i1 < N else i1 - 1
 
@@ -88,16 +88,17 @@ class Walk:
                 seen += range(p, p + n)
                 acc += float(y[p:p + n].sum())
                 if last:
+                    d = dest(row)
                     if cont:
-                        acc += slots["t"]
-                    if opened:
-                        slots["t"] = acc
+                        acc += slots[d] if isinstance(d, str) else A[d]
+                    if opened and not isinstance(d, str):
+                        A[d] = acc  # the row of A itself holds the sum of its first batches
                     else:
-                        put(dest(row), acc)
+                        put(d, acc)
                     acc = 0.0
             ib, crow, pb = inext, orow, pe
         assert seen == list(range(self.p0, self.p1))
-        if self.i1 < self.N and self.p1 <= self.rp[self.i1]:
+        if self.last and self.i1 < self.N and self.p1 <= self.rp[self.i1]:
             slots["t"] = 0.0
 
 
@@ -109,6 +110,66 @@ def shapes():
            "empty_tail": [99] * 10 + [2999], "window_edges": ([3] * 63 + [0]) * 6 + [70] * 130,
            "power": np.minimum((rng.pareto(1.1, 1500) * 3 * (rng.random(1500) < 0.6)).astype(int), 4000)}
     return out.items()
+
+
+def part(rowptr, N, nnz, S, k, q, parts):
+    """make_part: coordinates of part q of slice k and, of the first part, the head row."""
+    d0, d1 = k * S, min(k * S + S, N + nnz)
+    snap = snap_len(S)
+
+    def cut(d, ref):
+        lo = max(0, d - nnz)
+        i = max(x for x in range(lo, min(d, N) + 1) if rowptr[x] + x <= d)
+        if i >= N:
+            return i, nnz
+        r0, r1 = int(rowptr[i]), int(rowptr[i + 1])
+        return i, (ref - i if r0 + i < ref and r1 - r0 > snap else r0)
+
+    i0, p0 = cut(min(d0 + S * q // parts, d1), d0)
+    i1, p1 = cut(min(d0 + S * (q + 1) // parts, d1), d1 if q + 1 == parts else d0)
+    head = -1
+    if q == 0 and i0 < N and p0 > rowptr[i0] and rowptr[i0 + 1] + i0 + 1 <= d1:
+        head = i0
+    return i0, p0, i1, p1, head
+
+
+@pytest.mark.parametrize("parts", [1, 3, 5, 31])
+@pytest.mark.parametrize("workers", [1, 3, 40])
+@pytest.mark.parametrize("name,lengths", shapes())
+def test_parts_of_a_slice(name, lengths, workers, parts):
+    lengths = lengths[:700]
+    rowptr = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int64)
+    N, nnz = len(lengths), int(rowptr[-1])
+    y = np.random.default_rng(1).integers(1, 9, nnz).astype(float)
+    S = slice_len(N + nnz, workers, 64, N=N, nnz=nnz)
+    A, written, open_row = np.zeros(N), np.zeros(N, int), None
+    for k in range(-(-(N + nnz) // S)):
+        at = slice_bounds(rowptr, N, nnz, S, k * S, snap_len(S))
+        end = slice_bounds(rowptr, N, nnz, S, min(k * S + S, N + nnz), snap_len(S))
+        slots, heads, head_row = {}, [], -1
+        for q in range(parts):
+            i0, p0, i1, p1, h = part(rowptr, N, nnz, S, k, q, parts)
+            assert (i0, p0) == at and (i1, p1) >= at  # parts follow one another
+            at, last = (i1, p1), q + 1 == parts
+            if q == 0:
+                head_row = h
+            w = Walk(rowptr, N, i0, p0, i1, p1, 64, last)
+            heads += [i0] if w.head else []
+            mine = {}
+            w.run(8, y, A, written, mine)
+            assert last or "t" not in mine
+            assert not slots.keys() & mine.keys()
+            slots.update(mine)
+        assert at == end and heads == ([head_row] if head_row >= 0 else [])
+        if head_row >= 0:
+            assert open_row is not None and open_row[0] == head_row and written[head_row] == 0
+            A[head_row], written[head_row] = open_row[1] + slots["h"], 1
+            open_row = None
+        if end[0] < N:
+            base = open_row[1] if open_row and open_row[0] == end[0] else 0.0
+            open_row = (end[0], base + slots["t"])
+    assert written.all()
+    assert np.array_equal(A, [y[a:b].sum() for a, b in zip(rowptr, rowptr[1:])])
 
 
 @pytest.mark.parametrize("cap", [64, 512])

@@ -83,3 +83,24 @@ def test_more_columns_than_24_bits(gpu):
                                    (256, 256, 1 << 17), (16, 256, 246724), (16, 256, 246723)])
 def test_kernels_chosen_by_size(gpu, K, L, M):
     run_large(gpu, 3000, 21, M, K, L)
+
+
+# wide rows, whose slices several waves share: three and five parts, hub rows over
+# many slices, rows that begin in one slice and end in the parts of a later one
+@pytest.mark.parametrize("K,L,N,mean", [(128, 128, 70_001, 30), (5, 260, 150_000, 40), (96, 3, 330_007, 12),
+                                        (3, 96, 400_000, 20)])
+def test_parts(gpu, K, L, N, mean):
+    import torch
+    n = power_law_lengths(N, seed=L, cap=4000)
+    n = n * mean * N // int(n.sum())
+    n[[7, N // 3, N - 1]] = 300_000, 20_000, 9_000
+    n[N // 2:N // 2 + 5000] = 0
+    p = make_problem(n, 4099, K, L, seed=K, dups=True, dense="normal")
+    d = upload(p)
+    check_A_rows(p, fused(d), what="fused")
+    Y, A = unfused(d)
+    check_Y(p, Y)
+    check_A_rows(p, A, what="unfused")
+    A = torch.full_like(A, float("nan"))
+    slnr.sparselnr_fused_sddmm_spmm_noalloc(*(d[k] for k in ("rowptr", "colidx", "vals", "C", "D", "E")), A)
+    check_A_rows(p, A, what="noalloc")
