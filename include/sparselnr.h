@@ -255,7 +255,8 @@ SPARSELNR_API int sparselnr_last_hip_error(void);
  * more, shorter slices: the workers resident at one moment then cover a
  * narrower band of rows, which changes how D and E rows are shared in the
  * caches.  factor 0 restores the automatic choice (by the number of rows per
- * resident worker and the widths; 1 for small matrices); 1..64 fixes the factor for every
+ * resident worker and the widths; 1 for small matrices; several waves may share
+ * a slice of wide rows then); 1..64 fixes the factor for every
  * later call in the process, on every device and stream (the environment
  * variable SPARSELNR_GRID_FACTOR gives the first value).  Results are
  * deterministic for a fixed factor; another factor splits rows between slices
