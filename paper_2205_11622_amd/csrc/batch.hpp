@@ -405,6 +405,10 @@ struct BatchWalk {
         ib, pb, pe,
         [&](int row, int s, int e) {
           float acc[4] = {0.f, 0.f, 0.f, 0.f};
+          // Long segments halve their rounding error by it (SpMM at L = 96, power-law rows:
+          // 2.0e-7 -> 1.2e-7).  Widths to 64 spread a row over four groups and more, and
+          // there 65536 rows of 16 ran 1% slower with the test alone.
+          const bool tall = G >= 32 && e - s > 4 * U * NPP;
           for (int k = s; k < e; k += U * NPP) {
             const int n = e - k;
             const int2 *zp = nz + (k - pb);
@@ -415,13 +419,16 @@ struct BatchWalk {
               for (int u = 0; u < U; ++u) z[u] = zp[u * NPP + g];
 #pragma unroll
               for (int u = 0; u < U; ++u) load_e(x[u], z[u].x);
-              // the four terms first: a chain of additions a quarter as long, and
-              // half the rounding error in rows of thousands
-              float t[4] = {0.f, 0.f, 0.f, 0.f};
+              if (tall) {  // uniform: the four terms first, a chain of additions a quarter as long
+                float t[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-              for (int u = 0; u < U; ++u) add(t, x[u], z[u]);
+                for (int u = 0; u < U; ++u) add(t, x[u], z[u]);
 #pragma unroll
-              for (int v = 0; v < 4; ++v) acc[v] += t[v];
+                for (int v = 0; v < 4; ++v) acc[v] += t[v];
+              } else {
+#pragma unroll
+                for (int u = 0; u < U; ++u) add(acc, x[u], z[u]);
+              }
             } else {
 #pragma unroll
               for (int u = 0; u < U; ++u)
