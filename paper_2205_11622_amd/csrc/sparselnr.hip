@@ -157,7 +157,7 @@ struct Variant {
   int block = kBlock;  // threads per block
   KernelFn fn_wide = nullptr;   // wider workers, for inputs that need several resident grids
   int W_wide = 64;
-  int tk = 1, tl = 1;  // batch walk: float4 columns of a tile
+  int tk = 1;          // batch walk: float4 columns of a tile of K
   int rows = 0;        // batch walk: rows per slice that the automatic grid aims at
   int64_t carry_row = 0;  // and bytes of carry per worker
   int part_rows = 0;      // rows per part of a slice (0: slices are not parted)
@@ -204,7 +204,10 @@ Variant epi_wl(int64_t Lout, int block) {
   return v;
 }
 
-// float4 columns of the equal tiles of a width.
+// float4 columns of the equal tiles of a width.  Each launch of an l-tile takes those
+// of its own width: equal tiles of more than 64 float4 columns have 32 and more each, so
+// the ragged last lane of a tile, which moves back to the last four columns, stays
+// inside it (the tiles of a row are added to A one after another).
 int batch_tile(int64_t width) {
   const int64_t q4 = (width + 3) / 4, n = (q4 + kBatchTile - 1) / kBatchTile;
   return n ? (int)((q4 + n - 1) / n) : 1;
@@ -223,7 +226,6 @@ Variant batch(int64_t M, int64_t K, int64_t L) {
   v.W = 64;
   v.block = kWalkBlock;
   v.tk = batch_tile(K);
-  v.tl = batch_tile(L < kBatchL ? L : kBatchL);
   v.rows = K + L < 256 ? 16 : 6;
   v.part_rows = K + L >= 256 ? 3 : K >= 96 || L >= 96 ? 6 : 0;
   v.carry_row = MODE == kSddmm ? 0 : 2 * (L < kBatchL ? L : kBatchL) * 4 + 8;
@@ -551,7 +553,6 @@ int run_walk(Mode mode, const Variant *vs, const WalkArgs *as, int nv, hipStream
   a.xcd_span = g.xcd_span;
   a.xcds = kXcds;
   a.tk = v.tk;
-  a.tl = v.tl;
   a.parts = g.parts;
   if (mode != kSddmm) {
     const CarrySize cs = carry_size(g, tile_w);
@@ -570,6 +571,7 @@ int run_walk(Mode mode, const Variant *vs, const WalkArgs *as, int nv, hipStream
   for (int64_t t = 0; t < (mode == kSddmm ? 1 : tiles); ++t) {
     a.l0 = (int32_t)(t * tile_w);
     a.Lw = (int32_t)((a.L - a.l0) < tile_w ? (a.L - a.l0) : tile_w);
+    a.tl = batch_tile(a.Lw);
     for (int k = 0; k < nv; ++k) {
       WalkArgs ak = as[k];  // the shared fields come from a
       ak.workers = a.workers;

@@ -197,3 +197,34 @@ def test_every_nonzero_and_row_once(name, lengths, workers, cap):
                 open_row = (i1, base + slots["t"])
         assert written.all()
         assert np.array_equal(A, [y[a:b].sum() for a, b in zip(rowptr, rowptr[1:])])
+
+
+BATCH_TILE, BATCH_L = 64, 512  # kBatchTile, kBatchL
+
+
+def batch_tile(width):
+    q4 = -(-width // 4)
+    n = -(-q4 // BATCH_TILE)
+    return -(-q4 // n) if n else 1
+
+
+def tiles_of_launches(L):
+    """Columns that the lanes of each tile of each launch store, as run_walk and BatchWalk::rows cut them."""
+    for l0 in range(0, L, BATCH_L):
+        Lw = min(L - l0, BATCH_L)
+        q4, tl = -(-Lw // 4), batch_tile(Lw)
+        for q0 in range(0, q4, tl):
+            cols = set()
+            for q in range(min(tl, q4 - q0)):
+                first = 4 * (q0 + q)
+                valid = Lw - first
+                col = Lw - 4 if valid < 4 <= Lw else first
+                cols.update(range(l0 + col, l0 + col + (4 if Lw >= 4 else valid)))
+            yield cols
+
+
+def test_no_column_in_two_tiles():
+    # a row's sums are added to A tile by tile: a column in two of them would be added twice
+    for L in range(1, 3000):
+        seen = [c for cols in tiles_of_launches(L) for c in cols]
+        assert sorted(seen) == list(range(L)), L

@@ -104,3 +104,21 @@ def test_parts(gpu, K, L, N, mean):
     A = torch.full_like(A, float("nan"))
     slnr.sparselnr_fused_sddmm_spmm_noalloc(*(d[k] for k in ("rowptr", "colidx", "vals", "C", "D", "E")), A)
     check_A_rows(p, A, what="noalloc")
+
+
+# widths of more than one launch (512 columns) whose last launch has 257 to 259 columns, and
+# one beside them: 65 float4 columns, which tiles of 64 would leave one lane over
+@pytest.mark.parametrize("L", [769, 770, 771, 772, 1283])
+def test_tiles_of_the_last_launch(gpu, L):
+    # slices of 700 items, so most of them have a row that goes on in a second batch
+    n = np.full(40_000, 110)
+    n[5], n[20_000] = 90_000, 4_000
+    p = make_problem(n, 211, 3, L, seed=L, dups=True)
+    d = upload(p)
+    rows = np.concatenate([np.arange(0, 40_000, 23), [5, 20_000]])
+    try:
+        slnr.sparselnr_set_grid_factor(1)
+        check_A_rows(p, fused(d), rows=rows, what="fused")
+        check_A_rows(p, unfused(d)[1], rows=rows, what="unfused")
+    finally:
+        slnr.sparselnr_set_grid_factor(0)
