@@ -289,21 +289,26 @@ struct BatchWalk {
     const int first = 4 * (q0 + (lane_in ? q : nq - 1));  // lanes past nq repeat the last one's loads
     const int valid = a.K - first;
     // the last lane of a ragged width reads the last four floats and drops
-    // those that the lane before it has
+    // those that the lane before it has: of C as of D, for an infinity in the one
+    // times the other's zero would be no number
     const int col = TAIL && valid < 4 && a.K >= 4 ? a.K - 4 : first;
     const int drop = first - col;
+    auto drop_front = [&](float (&x)[4]) {
+      if constexpr (TAIL) {
+#pragma unroll
+        for (int v = 0; v < 3; ++v) x[v] = v < drop ? 0.f : x[v];
+      }
+    };
     auto load_c = [&](float (&c)[4], int row) {
       ld_cols<TAIL, true>(c, a.C, row, a.K, col, a.K >= 4, valid);
+      drop_front(c);
     };
     auto load_d = [&](float (&x)[4], int j) {
       ld_cols<TAIL, BIG>(x, a.D, j, a.K, col, a.K >= 4, valid);
     };
     // all lanes of a group hold the sum and write the same word
     auto finish = [&](const float (&c)[4], float (&x)[4], int2 z, int2 *at) {
-      if constexpr (TAIL) {
-#pragma unroll
-        for (int v = 0; v < 3; ++v) x[v] = v < drop ? 0.f : x[v];
-      }
+      drop_front(x);
       float t = 0.f;
 #pragma unroll
       for (int v = 0; v < 4; ++v) t = fmaf(c[v], x[v], t);

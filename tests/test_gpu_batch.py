@@ -122,3 +122,32 @@ def test_tiles_of_the_last_launch(gpu, L):
         check_A_rows(p, unfused(d)[1], rows=rows, what="unfused")
     finally:
         slnr.sparselnr_set_grid_factor(0)
+
+
+# every ragged width of a tile, one and two tiles of K, one and two launches of L
+@pytest.mark.parametrize("K,L", [(5, 6), (6, 7), (7, 5), (9, 67), (130, 3), (3, 130), (66, 259), (259, 66), (515, 769)])
+def test_infinities_and_nan(gpu, K, L):
+    """Where a sum is infinite or not a number in 64 bits it is so in the result, and nowhere else."""
+    import torch
+    n = np.tile([1, 3, 17, 40, 130, 0, 7], 40)
+    p = make_problem(n, 97, K, L, seed=L, dups=True, dense="normal")
+    row = np.repeat(np.arange(p.N), n)
+    for what in "CDE":  # one value in a row of the operand, its column another in each row
+        q = make_problem(n, 97, K, L, seed=L, dups=True, dense="normal")
+        X = getattr(q, what)
+        for r in range(0, X.shape[0], 3 if what == "C" else 8):
+            X[r, (r * 5 + 1) % X.shape[1]] = (np.inf, -np.inf, np.nan)[r % 7 % 3]
+        d = upload(q)
+        with np.errstate(invalid="ignore"):
+            Y = q.vals * (q.C[row].astype(float) * q.D[q.colidx]).sum(1)
+            A = np.zeros((q.N, L))
+            np.add.at(A, row, Y[:, None] * q.E[q.colidx])
+        got_Y, got_u = unfused(d)
+        for got, ref in ((fused(d), A), (got_u, A), (got_Y, Y)):
+            got, ref = got.cpu(), torch.from_numpy(ref)
+            ends = ~torch.isfinite(ref)
+            assert ends.any() or (what == "E" and ref.dim() == 1)  # the SDDMM does not read E
+            assert torch.equal(torch.isfinite(got), ~ends), what
+            assert torch.equal(got[ends].isnan(), ref[ends].isnan()), what
+            inf = ref.isinf()
+            assert torch.equal(got[inf].double(), ref[inf]), what
