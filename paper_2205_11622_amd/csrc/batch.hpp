@@ -119,13 +119,13 @@ __device__ __forceinline__ int value_of(int lane) {
 // Floats col .. col+3 of row j; of a row too narrow for that (not `wide`) only
 // the first `valid`.
 template <bool TAIL, bool BIG>
-__device__ __forceinline__ void ld_cols(float (&r)[4], const float *base, int j, int64_t stride,
+__device__ __forceinline__ void ld_cols(float (&r)[4], const float *base, uint32_t j, int64_t stride,
                                         int col, bool wide, int valid) {
   const float *p;
   if constexpr (BIG) {
     p = base + (int64_t)j * stride + col;
   } else {
-    const uint32_t off = __umul24((uint32_t)j, (uint32_t)stride * 4u) + (uint32_t)col * 4u;
+    const uint32_t off = __umul24(j, (uint32_t)stride * 4u) + (uint32_t)col * 4u;
     p = reinterpret_cast<const float *>(reinterpret_cast<const char *>(base) + off);
   }
   if (!TAIL || wide) {  // uniform
@@ -203,27 +203,33 @@ __device__ __forceinline__ Part make_part(const WalkArgs &a) {
   return s;
 }
 
+// No row: not an index below 2^31.
+constexpr uint32_t kNoRow = ~0u;
+
 // TAIL: K or L is no multiple of 4.  BIG: 64-bit row offsets.
+//
+// Rows and nonzeros are counted in unsigned 32 bits: both stay below 2^31, and the
+// steps past the last of them (64 rows of a window, 64 nonzeros of a burst) do not wrap.
 template <int MODE, bool TAIL, bool BIG>
 struct BatchWalk {
   const WalkArgs &a;
   int2 *nz;
   int lane;
-  int i0, p0, i1, p1;  // the part
+  uint32_t i0, p0, i1, p1;  // the part
   bool head;
-  int rlast;           // last row with a segment in the part
+  uint32_t rlast;           // last row with a segment in the part
   float *head_slot, *tail_slot;
-  int wrb;             // rowptr window: row wrb + lane covers ws .. we of the slice
-  int ws, we;
+  uint32_t wrb;             // rowptr window: row wrb + lane covers ws .. we of the slice
+  uint32_t ws, we;
 
   __device__ __forceinline__ BatchWalk(const WalkArgs &a_, int2 *nz_) : a(a_), nz(nz_) {}
 
-  __device__ __forceinline__ void window(int rb) {
+  __device__ __forceinline__ void window(uint32_t rb) {
     if (rb == wrb) return;
     wrb = rb;
-    const int r = rb + lane;
+    const uint32_t r = rb + lane;
     const bool in = r <= rlast;
-    const int x = in ? a.rowptr[r] : 0, y = in ? a.rowptr[r + 1] : 0;
+    const uint32_t x = in ? a.rowptr[r] : 0, y = in ? a.rowptr[r + 1] : 0;
     ws = x > p0 ? x : p0;
     we = y < p1 ? y : p1;
     if (!in) ws = we = 0;
@@ -235,13 +241,15 @@ struct BatchWalk {
   // Rows of 10 nonzeros, one after another, would leave three of the four
   // gathers of a lane unused: in sets they run 1.2-1.4x faster at K = L = 16.
   template <int NPP, typename One, typename Several>
-  __device__ __forceinline__ void for_rows(int ib, int pb, int pe, One one, Several several) {
-    for (int rb = ib;; rb += 64) {
+  __device__ __forceinline__ void for_rows(uint32_t ib, uint32_t pb, uint32_t pe, One one,
+                                           Several several) {
+    for (uint32_t rb = ib;; rb += 64) {
       window(rb);
-      const int vs = ws > pb ? ws : pb, ve = we < pe ? we : pe;
-      uint64_t mask = __ballot(ve > vs);
-      const uint64_t tall4 = __ballot(ve - vs > NPP), tall2 = __ballot(ve - vs > 2 * NPP);
-      const bool more = rb + 63 < rlast && __builtin_amdgcn_readlane(we, 63) < pe;
+      const uint32_t vs = ws > pb ? ws : pb, ve = we < pe ? we : pe;
+      const int len = (int)(ve - vs);  // 0 or less: nothing of this row
+      uint64_t mask = __ballot(len > 0);
+      const uint64_t tall4 = __ballot(len > NPP), tall2 = __ballot(len > 2 * NPP);
+      const bool more = rb + 63 < rlast && (uint32_t)__builtin_amdgcn_readlane(we, 63) < pe;
       // the next R rows, if there are that many and none is in `tall`
       auto set = [&](auto r, uint64_t tall) {
         constexpr int R = decltype(r)::value;
@@ -280,7 +288,7 @@ struct BatchWalk {
   // the K floats: y = b * dot if `whole` (that is all of K; y holds b before),
   // else added to y.
   template <int G>
-  __device__ __forceinline__ void dots(int ib, int pb, int pe, int q0, int nq, bool whole) {
+  __device__ __forceinline__ void dots(uint32_t ib, uint32_t pb, uint32_t pe, int q0, int nq, bool whole) {
     constexpr int NPP = 64 / G, U = 4;
     int ln = lane;
     asm volatile("" : "+v"(ln));  // keeps the lane's indices out of the registers of other phases
@@ -299,7 +307,7 @@ struct BatchWalk {
         for (int v = 0; v < 3; ++v) x[v] = v < drop ? 0.f : x[v];
       }
     };
-    auto load_c = [&](float (&c)[4], int row) {
+    auto load_c = [&](float (&c)[4], uint32_t row) {
       ld_cols<TAIL, true>(c, a.C, row, a.K, col, a.K >= 4, valid);
       drop_front(c);
     };
@@ -318,11 +326,11 @@ struct BatchWalk {
     };
     for_rows<NPP>(
         ib, pb, pe,
-        [&](int row, int s, int e) {
+        [&](uint32_t row, uint32_t s, uint32_t e) {
           float c[4];
           load_c(c, row);
-          for (int k = s; k < e; k += U * NPP) {
-            const int n = e - k;
+          for (uint32_t k = s; k < e; k += U * NPP) {
+            const int n = (int)(e - k);
             int2 *zp = nz + (k - pb);
             int2 z[U];
             float x[U][4];
@@ -347,7 +355,7 @@ struct BatchWalk {
             }
           }
         },
-        [&](auto r, int rb, i4_t b, i4_t s, i4_t e) {
+        [&](auto r, uint32_t rb, i4_t b, i4_t s, i4_t e) {
           constexpr int R = decltype(r)::value, S = U / R;  // S passes a row
           int2 *zp[U];
           int2 z[U];
@@ -355,7 +363,7 @@ struct BatchWalk {
 #pragma unroll
           for (int u = 0; u < U; ++u) {
             const int n = e[u / S] - s[u / S], k = u % S * NPP + g;
-            zp[u] = nz + (s[u / S] - pb + (k < n ? k : n - 1));
+            zp[u] = nz + ((int)(s[u / S] - pb) + (k < n ? k : n - 1));
             z[u] = *zp[u];
           }
 #pragma unroll
@@ -368,16 +376,17 @@ struct BatchWalk {
   }
 
   // Where the sums of a row go (column l0 of it), also those of a first batch of it.
-  __device__ __forceinline__ float *row_at(int row) const {
+  __device__ __forceinline__ float *row_at(uint32_t row) const {
     return row == i1           ? tail_slot
            : row == i0 && head ? head_slot
                                : a.out + (int64_t)row * a.L + a.l0;
   }
 
   // Columns l0 + [4 * q0, 4 * q0 + 4 * nq) of the rows of the batch.  crow: the
-  // row begun in an earlier batch of the part (-1: none).
+  // row begun in an earlier batch of the part, or kNoRow.
   template <int G>
-  __device__ __forceinline__ void rows(int ib, int pb, int pe, int q0, int nq, int crow) {
+  __device__ __forceinline__ void rows(uint32_t ib, uint32_t pb, uint32_t pe, int q0, int nq,
+                                       uint32_t crow) {
     constexpr int NPP = 64 / G, U = 4;
     int ln = lane;
     asm volatile("" : "+v"(ln));
@@ -408,14 +417,14 @@ struct BatchWalk {
     };
     for_rows<NPP>(
         ib, pb, pe,
-        [&](int row, int s, int e) {
+        [&](uint32_t row, uint32_t s, uint32_t e) {
           float acc[4] = {0.f, 0.f, 0.f, 0.f};
           // Long segments halve their rounding error by it (SpMM at L = 96, power-law rows:
           // 2.0e-7 -> 1.2e-7).  Widths to 64 spread a row over four groups and more, and
           // there 65536 rows of 16 ran 1% slower with the test alone.
-          const bool tall = G >= 32 && e - s > 4 * U * NPP;
-          for (int k = s; k < e; k += U * NPP) {
-            const int n = e - k;
+          const bool tall = G >= 32 && (int)(e - s) > 4 * U * NPP;
+          for (uint32_t k = s; k < e; k += U * NPP) {
+            const int n = (int)(e - k);
             const int2 *zp = nz + (k - pb);
             int2 z[U];
             float x[U][4];
@@ -460,7 +469,7 @@ struct BatchWalk {
             store(dst, acc);
           }
         },
-        [&](auto r, int rb, i4_t b, i4_t s, i4_t e) {
+        [&](auto r, uint32_t rb, i4_t b, i4_t s, i4_t e) {
           constexpr int R = decltype(r)::value, S = U / R;
           if constexpr (G <= 64 / R) {
             int2 z[U];
@@ -468,7 +477,7 @@ struct BatchWalk {
 #pragma unroll
             for (int u = 0; u < U; ++u) {
               const int n = e[u / S] - s[u / S], k = u % S * NPP + g;
-              z[u] = nz[s[u / S] - pb + (k < n ? k : n - 1)];
+              z[u] = nz[(int)(s[u / S] - pb) + (k < n ? k : n - 1)];
             }
 #pragma unroll
             for (int u = 0; u < U; ++u) load_e(x[u], z[u].x);
@@ -479,7 +488,7 @@ struct BatchWalk {
 #pragma unroll
             for (int v = 0; v < 4; ++v) o[v] = groups_sum_of<R, G>(acc, v);
             const int k = value_of<R>(ln);
-            int row = rb + (k == 0 ? b.x : b.y);
+            uint32_t row = rb + (k == 0 ? b.x : b.y);
             if constexpr (R == 4) row = k < 2 ? row : rb + (k == 2 ? b.z : b.w);
             if (lane_in && (ln & (64 / R - 1)) < G) {
               float *dst = row_at(row) + col;
@@ -496,11 +505,11 @@ struct BatchWalk {
 
   // Zero rows (or partial rows) of the segments without a nonzero.
   __device__ __forceinline__ void zeros() {
-    for (int rb = i0; rb <= rlast; rb += 64) {
+    for (uint32_t rb = i0; rb <= rlast; rb += 64) {
       window(rb);
       uint64_t m = __ballot(rb + lane <= rlast && rb + lane != i1 && we <= ws);
       while (m) {
-        const int row = rb + __builtin_ctzll(m);
+        const uint32_t row = rb + __builtin_ctzll(m);
         m &= m - 1;
         float *dst = row_at(row);
         for (int l = lane; l < a.Lw; l += 64) __builtin_nontemporal_store(0.f, dst + l);
@@ -519,12 +528,12 @@ struct BatchWalk {
     rlast = i1 < a.N ? i1 : i1 - 1;
     head_slot = a.carry + (int64_t)id * 2 * a.Lw;
     tail_slot = head_slot + a.Lw;
-    wrb = -1;
+    wrb = kNoRow;
     if constexpr (MODE != kSddmm) zeros();
-    int ib = i0, crow = -1;
-    for (int pb = p0; pb < p1;) {
-      const int pe = p1 - pb < kBatch ? p1 : pb + kBatch;
-      const int n = pe - pb;
+    uint32_t ib = i0, crow = kNoRow;
+    for (uint32_t pb = p0; pb < p1;) {
+      const uint32_t pe = p1 - pb < kBatch ? p1 : pb + kBatch;
+      const int n = (int)(pe - pb);
       const int qk = (a.K + 3) >> 2;
       const bool whole = MODE == kSpmm || qk <= a.tk;  // one tile holds all of K
       int2 z[kBatch / 64];
@@ -541,7 +550,7 @@ struct BatchWalk {
       for (int t = 0; t < kBatch / 64; ++t)
         if (t * 64 + lane < n) nz[t * 64 + lane] = z[t];
       // the first row with nonzeros from pe on, and whether it has some before
-      int inext = ib, orow = -1;
+      uint32_t inext = ib, orow = kNoRow;
       if (pe < p1) {
         while (inext <= rlast) {
           window(inext);
@@ -549,7 +558,7 @@ struct BatchWalk {
           if (m) {
             const int b = __builtin_ctzll(m);
             inext += b;
-            if (__builtin_amdgcn_readlane(ws, b) < pe) orow = inext;
+            if ((uint32_t)__builtin_amdgcn_readlane(ws, b) < pe) orow = inext;
             break;
           }
           inext += 64;
@@ -589,12 +598,12 @@ struct BatchWalk {
       crow = orow;
       pb = pe;
     }
-    if (MODE != kSddmm && s.last && i1 < a.N && p1 <= a.rowptr[i1]) {  // an empty tail
+    if (MODE != kSddmm && s.last && i1 < a.N && p1 <= (uint32_t)a.rowptr[i1]) {  // an empty tail
       for (int l = lane; l < a.Lw; l += 64) tail_slot[l] = 0.f;
     }
     if (MODE != kSddmm && lane == 0) {
       int32_t *meta = a.meta + 2 * (int64_t)id;
-      if (s.last) meta[0] = i1 < a.N ? i1 : -1;
+      if (s.last) meta[0] = i1 < a.N ? (int)i1 : -1;
       if (s.first) meta[1] = s.head_row;
     }
   }

@@ -9,6 +9,11 @@ import pytest
 from tests.test_partition import slice_bounds, slice_len, snap_len
 
 
+def index(x):
+    """The kernel's row and nonzero counters: unsigned, 32 bits."""
+    return x & 0xFFFFFFFF
+
+
 class Walk:
     def __init__(self, rowptr, N, i0, p0, i1, p1, cap, last=True):
         self.rp, self.N, self.i0, self.p0, self.i1, self.p1 = rowptr, N, i0, p0, i1, p1
@@ -19,9 +24,9 @@ class Walk:
     def window(self, rb):
         ws, we = [], []
         for lane in range(64):
-            r = rb + lane
+            r = index(rb + lane)
             if r <= self.rlast:
-                assert 0 <= r < self.N  # reads rowptr[r], rowptr[r + 1]
+                assert rb <= r < self.N  # reads rowptr[r], rowptr[r + 1]
                 ws.append(max(int(self.rp[r]), self.p0))
                 we.append(min(int(self.rp[r + 1]), self.p1))
             else:
@@ -37,15 +42,15 @@ class Walk:
             for b in range(64):
                 s, e = max(ws[b], pb), min(we[b], pe)
                 p = s
-                while p < e:
+                while p < e:  # p is compared past the row's end, too
                     n = min(npp, e - p)
                     row = rb + b
                     yield (p, n, row, p == s, p + n == e, ws[b] < pb,
                            row == self.i1 or we[b] > pe)
-                    p += n
-            if not (rb + 63 < self.rlast and we[63] < pe):
+                    p = index(p + npp) if index(p + npp) < e else e
+            if not (index(rb + 63) < self.rlast and we[63] < pe):
                 return
-            rb += 64
+            rb = index(rb + 64)
 
     def run(self, npp, y, A, written, slots):
         """One column: A[row] or the slice's head / tail slot gets the sums."""
@@ -58,11 +63,13 @@ class Walk:
                 assert written[d] == 0
                 A[d], written[d] = v, 1
 
-        for rb in range(self.i0, self.rlast + 1, 64):
+        rb = self.i0
+        while rb <= self.rlast:
             ws, we = self.window(rb)
             for b in range(64):
-                if rb + b <= self.rlast and rb + b != self.i1 and we[b] <= ws[b]:
+                if index(rb + b) <= self.rlast and rb + b != self.i1 and we[b] <= ws[b]:
                     put(dest(rb + b), 0.0)
+            rb = index(rb + 64)
         ib, pb, crow, seen = self.i0, self.p0, -1, []
         while pb < self.p1:
             pe = min(self.p1, pb + self.cap)
@@ -70,13 +77,13 @@ class Walk:
             if pe < self.p1:
                 while inext <= self.rlast:
                     ws, we = self.window(inext)
-                    m = [b for b in range(64) if inext + b <= self.rlast and we[b] > pe]
+                    m = [b for b in range(64) if index(inext + b) <= self.rlast and we[b] > pe]
                     if m:
                         inext += m[0]
                         if ws[m[0]] < pe:
                             orow = inext
                         break
-                    inext += 64
+                    inext = index(inext + 64)
                 assert inext <= self.rlast
             acc = 0.0
             for p, n, row, first, last, cont, opened in self.passes(ib, pb, pe, npp):
@@ -228,3 +235,28 @@ def test_no_column_in_two_tiles():
     for L in range(1, 3000):
         seen = [c for cols in tiles_of_launches(L) for c in cols]
         assert sorted(seen) == list(range(L)), L
+
+
+class At(dict):
+    """A long array that is held only where it matters: 0 elsewhere."""
+    def __missing__(self, i):
+        return 0
+
+
+@pytest.mark.parametrize("rows", [1, 63, 64, 65, 130])
+def test_rows_up_to_the_index_limit(rows):
+    N = (1 << 31) - 2 - rows % 3
+    rp = At({N: 1})
+    A, written = At(), At()
+    w = Walk(rp, N, N - rows, 0, N, 1, 512)
+    w.run(8, np.ones(1), A, written, {})
+    assert sorted(written) == list(range(N - rows, N)) and A[N - 1] == 1.0
+
+
+@pytest.mark.parametrize("npp", [1, 16])
+def test_nonzeros_up_to_the_index_limit(npp):
+    nnz = (1 << 31) - 2
+    w = Walk([0, nnz], 1, 0, nnz - 700, 1, nnz, 512)
+    w.head = False  # the last slice of the row, without its carry
+    p = [x for pb, pe in ((nnz - 700, nnz - 188), (nnz - 188, nnz)) for x in w.passes(0, pb, pe, npp)]
+    assert sum(x[1] for x in p) == 700 and p[-1][0] + p[-1][1] == nnz

@@ -151,3 +151,43 @@ def test_infinities_and_nan(gpu, K, L):
             assert torch.equal(got[ends].isnan(), ref[ends].isnan()), what
             inf = ref.isinf()
             assert torch.equal(got[inf].double(), ref[inf]), what
+
+
+def test_rows_up_to_the_index_limit(gpu):
+    # N + nnz = 2^31 - 1, the nonzeros in the last rows
+    import torch
+    N, n = (1 << 31) - 9, 8
+    rowptr = torch.zeros(N + 1, dtype=torch.int32, device=gpu)
+    rowptr[N - 5:] = torch.tensor([0, 3, 3, 4, 7, n], dtype=torch.int32, device=gpu)
+    col = torch.arange(n, dtype=torch.int32, device=gpu) % 3
+    vals = torch.arange(1, n + 1, dtype=torch.float32, device=gpu)
+    C = torch.zeros(N, 1, device=gpu)
+    C[N - 4:] = torch.tensor([[2.], [3.], [5.], [7.]], device=gpu)
+    D = torch.tensor([[1.], [2.], [4.]], device=gpu)
+    C[N - 5] = 1
+    row = torch.tensor([0, 0, 0, 2, 3, 3, 3, 4], device=gpu)
+    Yref = vals * C[N - 5:][row, 0] * D[col.long(), 0]
+    Aref = torch.zeros(5, device=gpu).index_add_(0, row, Yref * D[col.long(), 0])
+    assert torch.equal(slnr.sparselnr_sddmm(rowptr, col, vals, C, D), Yref)  # small whole numbers: exact
+    A = torch.full((N, 1), float("nan"), device=gpu)
+    slnr.sparselnr_fused_sddmm_spmm(rowptr, col, vals, C, D, D, A)
+    assert torch.equal(A[N - 5:, 0], Aref)
+    assert int(torch.count_nonzero(A[:N - 5])) == 0
+    del A, C, rowptr
+    torch.cuda.empty_cache()
+
+
+def test_nonzeros_up_to_the_index_limit(gpu):
+    import torch
+    n = (1 << 31) - 2
+    rowptr = torch.tensor([0, n], dtype=torch.int32, device=gpu)
+    col = torch.zeros(n, dtype=torch.int32, device=gpu)
+    col[-1] = 1
+    vals = torch.ones(n, device=gpu)
+    C, D = torch.full((1, 1), 2., device=gpu), torch.tensor([[1.], [3.]], device=gpu)
+    Y = slnr.sparselnr_sddmm(rowptr, col, vals, C, D)
+    assert bool((Y[:-1] == 2).all()) and float(Y[-1]) == 6
+    E = torch.tensor([[0.], [5.]], device=gpu)  # the last nonzero alone counts
+    assert float(slnr.sparselnr_spmm(rowptr, col, Y, E)) == 30
+    del col, vals, Y
+    torch.cuda.empty_cache()
