@@ -203,6 +203,13 @@ __device__ __forceinline__ Part make_part(const WalkArgs &a) {
   return s;
 }
 
+// What a lane wrote before, to LDS or to A, the others of the wave read after.  The memory
+// operations of a wave are carried out in order, so it costs no instruction: it keeps the
+// compiler from moving them past each other.
+__device__ __forceinline__ void lanes_ordered() {
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+}
+
 // No row: not an index below 2^31.
 constexpr uint32_t kNoRow = ~0u;
 
@@ -314,7 +321,8 @@ struct BatchWalk {
     auto load_d = [&](float (&x)[4], int j) {
       ld_cols<TAIL, BIG>(x, a.D, j, a.K, col, a.K >= 4, valid);
     };
-    // all lanes of a group hold the sum and write the same word
+    // all lanes of a group hold the sum and write the same word, as do the groups that
+    // repeat a nonzero (all have read it by then)
     auto finish = [&](const float (&c)[4], float (&x)[4], int2 z, int2 *at) {
       drop_front(x);
       float t = 0.f;
@@ -339,6 +347,7 @@ struct BatchWalk {
               for (int u = 0; u < U; ++u) z[u] = zp[u * NPP + g];
 #pragma unroll
               for (int u = 0; u < U; ++u) load_d(x[u], z[u].x);
+              lanes_ordered();
 #pragma unroll
               for (int u = 0; u < U; ++u) finish(c, x[u], z[u], zp + (u * NPP + g));
             } else {  // groups past the row's end repeat its last nonzero
@@ -349,6 +358,7 @@ struct BatchWalk {
 #pragma unroll
               for (int u = 0; u < U; ++u)
                 if (u * NPP < n) load_d(x[u], z[u].x);
+              lanes_ordered();
 #pragma unroll
               for (int u = 0; u < U; ++u)
                 if (u * NPP < n) finish(c, x[u], z[u], zp + at(u));
@@ -370,6 +380,7 @@ struct BatchWalk {
           for (int u = 0; u < R; ++u) load_c(c[u], rb + b[u]);
 #pragma unroll
           for (int u = 0; u < U; ++u) load_d(x[u], z[u].x);
+          lanes_ordered();
 #pragma unroll
           for (int u = 0; u < U; ++u) finish(c[u / S], x[u], z[u], zp[u]);
         });
@@ -465,6 +476,7 @@ struct BatchWalk {
 #pragma unroll
               for (int v = 0; v < 4; ++v)
                 if (!TAIL || v < valid || a.Lw >= 4) acc[v] = dst[v] + acc[v];
+              if constexpr (TAIL) lanes_ordered();  // the last lane reads what its neighbour stores
             }
             store(dst, acc);
           }
@@ -496,6 +508,7 @@ struct BatchWalk {
 #pragma unroll
                 for (int v = 0; v < 4; ++v)
                   if (!TAIL || v < valid || a.Lw >= 4) o[v] = dst[v] + o[v];
+                if constexpr (TAIL) lanes_ordered();
               }
               store(dst, o);
             }
@@ -549,6 +562,7 @@ struct BatchWalk {
 #pragma unroll
       for (int t = 0; t < kBatch / 64; ++t)
         if (t * 64 + lane < n) nz[t * 64 + lane] = z[t];
+      lanes_ordered();
       // the first row with nonzeros from pe on, and whether it has some before
       uint32_t inext = ib, orow = kNoRow;
       if (pe < p1) {
@@ -572,6 +586,7 @@ struct BatchWalk {
           else if (nq <= 16) dots<16>(ib, pb, pe, q0, nq, whole);
           else if (nq <= 32) dots<32>(ib, pb, pe, q0, nq, whole);
           else dots<64>(ib, pb, pe, q0, nq, whole);
+          lanes_ordered();
         }
         if (!whole || qk == 0 || MODE == kSddmm) {
           for (int t = lane; t < n; t += 64) {
@@ -581,6 +596,7 @@ struct BatchWalk {
             if constexpr (MODE == kSddmm) a.out[pb + t] = y;
             else nz[t].y = __builtin_bit_cast(int, y);
           }
+          lanes_ordered();
         }
       }
       if constexpr (MODE != kSddmm) {
@@ -594,6 +610,7 @@ struct BatchWalk {
           else rows<64>(ib, pb, pe, q0, nq, crow);
         }
       }
+      lanes_ordered();  // the next batch's copy, and what it adds to a row of A
       ib = inext;
       crow = orow;
       pb = pe;

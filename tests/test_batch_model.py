@@ -3,6 +3,9 @@ batches, the rowptr windows and the passes over row segments, re-enacted on many
 CSR shapes.  Every nonzero of a part is passed once, in a pass of its own row;
 every row end is written exactly once, partial rows go through the slice's own
 slots, each of them written by one part, and every index stays inside its array."""
+import os
+import re
+
 import numpy as np
 import pytest
 
@@ -260,3 +263,17 @@ def test_nonzeros_up_to_the_index_limit(npp):
     w.head = False  # the last slice of the row, without its carry
     p = [x for pb, pe in ((nnz - 700, nnz - 188), (nnz - 188, nnz)) for x in w.passes(0, pb, pe, npp)]
     assert sum(x[1] for x in p) == 700 and p[-1][0] + p[-1][1] == nnz
+
+
+def test_phases_that_exchange_data_are_ordered():
+    """Between two phases of a batch in which one lane writes what another reads (the batch
+    in LDS, the dots beside it, the rows of A that go on in the next batch) stands an
+    ordering of the wave's memory operations."""
+    src = os.path.join(os.path.dirname(__file__), "..", "paper_2205_11622_amd", "csrc", "batch.hpp")
+    with open(src) as f:
+        run = f.read().split("void run(const Part &s)")[1]
+    phases = [r"nz\[t \* 64 \+ lane\] = z\[t\];", r"dots<64>\(", r"float y = .*nz\[t\]\.y", r"rows<64>\(", r"pb = pe;"]
+    at = [re.search(p, run).start() for p in phases]
+    assert at == sorted(at)
+    for a, b in zip(at, at[1:]):
+        assert "lanes_ordered();" in run[a:b], run[a:b]
