@@ -124,8 +124,8 @@ SPARSELNR_API int sparselnr_fused_sddmm_spmm(const int32_t *rowptr, const int32_
  * runs at the grid factor the fused entry point would use, halved until the
  * partial rows fit the array (so results may differ from the fused entry
  * point's in rounding order, within its accuracy; they are bit-identical
- * when the same factor fits, as it does at the automatic factor for the
- * workloads of this library).  It returns SPARSELNR_ERR_UNSUPPORTED if they
+ * when the same factor fits, as it does at the automatic factor for L up to
+ * 256).  It returns SPARSELNR_ERR_UNSUPPORTED if they
  * do not fit even at one resident grid (not reached for K, L <= 512).
  * All calls on one GPU share that GPU's array and it keeps the last call's
  * contents: calls that overlap in time on one GPU (different streams, or

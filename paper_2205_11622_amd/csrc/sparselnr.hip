@@ -35,6 +35,8 @@ constexpr int kBatchTile = 64;    // batch walk: at most 64 float4 columns per t
 constexpr int kMaxParts = 31;     // batch walk: at most 31 parts of a slice
 constexpr size_t kScratchBytes = SPARSELNR_NOALLOC_SCRATCH_BYTES;  // no-allocation device array
 constexpr int kBatchL = 512;      // batch walk: at most 512 columns of A per launch
+// Carry bytes of a worker up to which the automatic grid keeps to what fits that array: L = 256.
+constexpr int64_t kSameGridRow = 2 * 256 * 4 + 8;
 // <SpMMH, GEMM>: C .* D is formed once when nnz >= kHoistRatio * M (12 M J
 // bytes for the product against 4 J bytes per nonzero for a second gather).
 constexpr int64_t kHoistRatio = 3;
@@ -413,9 +415,13 @@ int blocks_per_cu(int dev, KernelFn fn, int block, size_t lds, int *out) {
 // rows fill the L2 of an XCD sooner (us at 1, 2, 4, 8, 16 grids; 27-point stencil of
 // 75^3, 64 rows a wave in one grid: K = L = 64 675, 503, 455, 457, 514, K = L = 128
 // 1611, 1405, 1252, 897, 794; 2^17 R-MAT vertices at 64 108, 112, 118, 129, 136; 100000
-// uniform rows of 16 at 64 114, 119, 121, 120, 128).  At most 24 grids, and no more
-// than 8 if the partial rows of more, `carry_row` bytes a worker, would not fit the
-// device array of the no-allocation entry point (which then takes the same grids).
+// uniform rows of 16 at 64 114, 119, 121, 120, 128).  At most 24 grids, and up to 256
+// columns no more than have their partial rows, `carry_row` bytes a worker, fit the
+// device array of the no-allocation entry point, which so takes the same grids and
+// rounds alike (8 grids / those that fit, us: 27-point stencils 128^3 at K = 16, L = 256
+// 4716 / 4689, 101^3 at 256 4088 / 4057, SpMM at 256 2146 / 2088, R-MAT and power-law
+// graphs at 256 within 2%).  Wider rows take up to 8 grids whether they fit or not: at
+// 512 two would be left, 50^3 at K = L = 512 998 / 1276, SpMM of 60^3 747 / 779.
 //
 // Wide rows (`part_rows` > 0) are walked by several waves a slice, each a part of it
 // (make_part): the rows that the waves of an XCD walk at one moment are then so few
@@ -437,7 +443,8 @@ Grid make_grid(int cus, int per_cu, int block, int W, int64_t N, int factor = 0,
   if (factor < 1 && rows > 0) {
     int64_t f = N / (resident_workers * rows);
     const int64_t fit = (int64_t)kScratchBytes / (resident_workers * (carry_row > 0 ? carry_row : 1));
-    const int64_t most = fit > kGridFactor ? (fit < 24 ? fit : 24) : kGridFactor;
+    const int64_t least = carry_row > kSameGridRow ? kGridFactor : 1;
+    const int64_t most = fit > least ? (fit < 24 ? fit : 24) : least;
     if (f > most) f = most;
     factor = f > 1 ? (int)f : 1;
   }

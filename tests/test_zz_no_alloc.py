@@ -85,3 +85,15 @@ def test_noalloc_lowers_the_grid_factor_to_fit(gpu):
     p2 = make_problem(small, 4_000, 32, 32, seed=44)
     print("then automatic: N=%d nnz=%d K=L=32" % (p2.N, p2.nnz), flush=True)
     check(p2, upload(p2), s, gpu, exact=True)
+
+
+@pytest.mark.parametrize("K,L", [(16, 256), (9, 252)])
+def test_noalloc_takes_the_grids_of_wide_rows(gpu, K, L):
+    """Enough rows for eight grids, whose partial rows would not fit the array from 170 columns on."""
+    import torch
+    s = torch.cuda.Stream()
+    n = power_law_lengths(420_000, seed=45, scale=1.0, cap=6_000)
+    n[[9, 200_000]] = 50_000, 20_000
+    p = make_problem(n, 30_000, K, L, seed=45, dups=True)
+    print("N=%d nnz=%d K=%d L=%d" % (p.N, p.nnz, K, L), flush=True)
+    check(p, upload(p), s, gpu, exact=True)
