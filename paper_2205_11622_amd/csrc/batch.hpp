@@ -145,16 +145,16 @@ __device__ __forceinline__ void ld_cols(float (&r)[4], const float *base, uint32
 // 16 at K = L = 128 2870 / 2915 / 2744, SpMM at 256 with 1M rows of 4 918 / 1024 / 840.
 constexpr uint32_t kPartItems = 80;
 
-__device__ __forceinline__ uint32_t parts_of(int64_t S, int most) {
-  if (S >= (int64_t)most * kPartItems) return (uint32_t)most;
-  const uint32_t fit = (uint32_t)S / kPartItems;
+__device__ __forceinline__ uint32_t parts_of(uint32_t S, uint32_t most) {
+  if (S >= most * kPartItems) return most;
+  const uint32_t fit = S / kPartItems;
   return fit > 1 ? fit | 1 : 1;
 }
 
 // One wave's share of a slice: part q of its parts.
 struct Part {
-  int64_t id;              // slice, and its carry slots
-  int64_t i0, p0, i1, p1;  // start and end coordinates
+  uint32_t id;              // slice, and its carry slots
+  uint32_t i0, p0, i1, p1;  // start and end coordinates
   bool head;               // row i0 began in an earlier slice and ends here
   bool first, last;        // part of the slice
   int head_row;            // of the first part: the slice's head row or -1
@@ -168,13 +168,14 @@ struct Part {
 // that row ends.  Part q of slice s comes right before part q + 1 on an XCD.
 __device__ __forceinline__ Part make_part(const WalkArgs &a) {
   Part s;
-  int64_t S, ns, items, nnz;
+  uint32_t S, ns, items, nnz;
   slice_count(a, &S, &ns, &items, &nnz);
-  const int64_t per_xcd = (ns + a.xcds - 1) / a.xcds;
-  const uint32_t in_xcd = blockIdx.x / (uint32_t)a.xcds;
-  const uint32_t parts = parts_of(S, a.parts);
+  const uint32_t N = (uint32_t)a.N, xcds = (uint32_t)a.xcds;
+  const uint32_t per_xcd = (ns + xcds - 1) / xcds;
+  const uint32_t in_xcd = blockIdx.x / xcds;
+  const uint32_t parts = parts_of(S, (uint32_t)a.parts);
   const uint32_t slice = in_xcd / parts, q = in_xcd % parts;
-  s.id = (int64_t)(blockIdx.x % (uint32_t)a.xcds) * per_xcd + slice;
+  s.id = blockIdx.x % xcds * per_xcd + slice;
   s.active = slice < per_xcd && s.id < ns;
   s.first = q == 0;
   s.last = q + 1 == parts;
@@ -182,23 +183,27 @@ __device__ __forceinline__ Part make_part(const WalkArgs &a) {
   s.head_row = -1;
   s.i0 = s.p0 = s.i1 = s.p1 = 0;
   if (!s.active) return s;
-  const int64_t d0 = s.id * S;
-  const int64_t d1 = d0 + S < items ? d0 + S : items;
-  const int64_t da = d0 + S * q / parts, db = d0 + S * (q + 1) / parts;
-  mp_search2<64>(a.rowptr, a.N, nnz, da < d1 ? da : d1, db < d1 ? db : d1, &s.i0, &s.i1);
+  const uint32_t d0 = s.id * S;
+  const uint32_t d1 = items - d0 > S ? d0 + S : items;
+  const uint32_t each = S / parts, over = S - each * parts;
+  auto cut = [&](uint32_t k) {  // the start of part k: S * k / parts items into the slice
+    const uint32_t d = d0 + each * k + over * k / parts;
+    return d < d1 ? d : d1;
+  };
+  mp_search2<64>(a.rowptr, N, nnz, cut(q), cut(q + 1), &s.i0, &s.i1);
   // Row i at the start of its nonzeros, or where the slice boundary `d` cuts it:
   // boundaries split rows of more than `snap` nonzeros only (as in make_slice).
-  const int64_t snap = snap_length(S);
-  auto at = [&](int64_t i, int64_t d) {
-    if (i >= a.N) return nnz;
-    const int64_t r0 = a.rowptr[i], r1 = a.rowptr[i + 1];
+  const uint32_t snap = snap_length(S);
+  auto at = [&](uint32_t i, uint32_t d) {
+    if (i >= N) return nnz;
+    const uint32_t r0 = a.rowptr[i], r1 = a.rowptr[i + 1];
     return r0 + i < d && r1 - r0 > snap ? d - i : r0;
   };
   s.p0 = at(s.i0, d0);
   s.p1 = at(s.i1, s.last ? d1 : d0);
-  if (s.i0 < a.N && s.p0 > (int64_t)a.rowptr[s.i0]) {
+  if (s.i0 < N && s.p0 > (uint32_t)a.rowptr[s.i0]) {
     s.head = s.i0 < s.i1;
-    if ((int64_t)a.rowptr[s.i0 + 1] + s.i0 + 1 <= d1) s.head_row = (int)s.i0;
+    if ((uint32_t)a.rowptr[s.i0 + 1] + s.i0 + 1 <= d1) s.head_row = (int)s.i0;
   }
   return s;
 }

@@ -231,38 +231,38 @@ __device__ __forceinline__ T ld_stream(const T *p) {
 // search takes log_G(N) steps instead of log_2(N) dependent loads, and the
 // two searches share their steps (both probes of a step are loaded before
 // either ballot).  All lanes of the group return the same values.
+// Rows, items and nonzeros are below 2^31 and counted in unsigned 32 bits.
 template <int G>
-__device__ __forceinline__ void mp_search2(const int32_t *rowptr, int64_t N, int64_t nnz,
-                                           int64_t da, int64_t db, int64_t *ia, int64_t *ib) {
-  const int lane = threadIdx.x & 63;
-  const int glane = lane & (G - 1);
-  const int gbase = lane - glane;
-  const int64_t d[2] = {da, db};
-  int64_t lo[2], hi[2];
+__device__ __forceinline__ void mp_search2(const int32_t *rowptr, uint32_t N, uint32_t nnz,
+                                           uint32_t da, uint32_t db, uint32_t *ia, uint32_t *ib) {
+  const uint32_t lane = threadIdx.x & 63;
+  const uint32_t glane = lane & (G - 1);
+  const uint32_t gbase = lane - glane;
+  const uint32_t d[2] = {da, db};
+  uint32_t lo[2], hi[2];
 #pragma unroll
   for (int t = 0; t < 2; ++t) {
     lo[t] = d[t] > nnz ? d[t] - nnz : 0;  // rowptr[lo] + lo <= d always holds
     hi[t] = d[t] < N ? d[t] : N;
   }
   while (lo[0] < hi[0] || lo[1] < hi[1]) {
-    int64_t step[2], x[2];
-    int32_t r[2];
+    uint32_t step[2], x[2], r[2];
 #pragma unroll
     for (int t = 0; t < 2; ++t) {  // a finished search probes its own end, which is in range
       step[t] = (hi[t] - lo[t] + G - 1) / G;
-      x[t] = lo[t] + (int64_t)(glane + 1) * step[t];
+      x[t] = lo[t] + (glane + 1) * step[t];
       if (x[t] > hi[t]) x[t] = hi[t];
     }
 #pragma unroll
-    for (int t = 0; t < 2; ++t) r[t] = rowptr[x[t]];
+    for (int t = 0; t < 2; ++t) r[t] = (uint32_t)rowptr[x[t]];
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
       if (lo[t] < hi[t]) {  // uniform in the group
-        const uint64_t ball = __ballot((int64_t)r[t] + x[t] <= d[t]);
+        const uint64_t ball = __ballot(r[t] + x[t] <= d[t]);
         const uint64_t bits = G == 64 ? ball : (ball >> gbase) & ((1ull << (G & 63)) - 1);
-        const int m = (~bits == 0) ? 64 : __builtin_ctzll(~bits);  // probes 0..m-1 hold
-        const int64_t xm1 = lo[t] + (int64_t)m * step[t];           // probe m-1 (if m > 0)
-        const int64_t xm = lo[t] + (int64_t)(m + 1) * step[t];      // probe m (if m < G)
+        const uint32_t m = (~bits == 0) ? 64 : __builtin_ctzll(~bits);  // probes 0..m-1 hold
+        const uint32_t xm1 = lo[t] + m * step[t];        // probe m-1 (if m > 0)
+        const uint32_t xm = lo[t] + (m + 1) * step[t];   // probe m (if m < G)
         if (m > 0) lo[t] = xm1 < hi[t] ? xm1 : hi[t];
         if (m < G) hi[t] = (xm < hi[t] ? xm : hi[t]) - 1;
       }
@@ -281,8 +281,8 @@ struct Slice {
 
 // Slice length of inputs too small to fill the GPU, and the row length that
 // slices shorter than 64 items still keep whole.
-constexpr int64_t kShortSlice = 16;
-constexpr int64_t kSnapRow = 16;
+constexpr uint32_t kShortSlice = 16;
+constexpr uint32_t kSnapRow = 16;
 
 // Slices are S = ceil(items / workers) items long, raised to min_chunk (or
 // to kShortSlice, below), so small inputs use only the first
@@ -303,13 +303,16 @@ constexpr int64_t kSnapRow = 16;
 // contiguous run of slices [x * ns / xcds, (x + 1) * ns / xcds), so that the
 // workers sharing an L2 walk neighbouring rows and every XCD gets an equal
 // share however small the input.
-__device__ __forceinline__ void slice_count(const WalkArgs &a, int64_t *S_out, int64_t *ns_out,
-                                            int64_t *items_out, int64_t *nnz_out) {
-  const int64_t nnz = a.rowptr[a.N];
-  const int64_t items = a.N + nnz;
-  int64_t S = (items + a.workers - 1) / a.workers;
-  if (S < kShortSlice && nnz <= kSnapRow * a.N) S = kShortSlice;
-  else if (S < a.min_chunk) S = a.min_chunk;
+//
+// All of it is unsigned 32-bit: N + nnz < 2^31, and a 64-bit division takes some 130
+// instructions of every wave's start, those launched in vain included.
+__device__ __forceinline__ void slice_count(const WalkArgs &a, uint32_t *S_out, uint32_t *ns_out,
+                                            uint32_t *items_out, uint32_t *nnz_out) {
+  const uint32_t nnz = (uint32_t)a.rowptr[a.N], N = (uint32_t)a.N;
+  const uint32_t items = N + nnz, workers = (uint32_t)a.workers;
+  uint32_t S = (items + workers - 1) / workers;
+  if (S < kShortSlice && nnz <= (uint64_t)kSnapRow * N) S = kShortSlice;
+  else if (S < (uint32_t)a.min_chunk) S = a.min_chunk;
   *S_out = S;
   *ns_out = (items + S - 1) / S;
   *items_out = items;
@@ -317,35 +320,38 @@ __device__ __forceinline__ void slice_count(const WalkArgs &a, int64_t *S_out, i
 }
 
 // Longest row that no boundary of slices of S items splits.
-__device__ __forceinline__ int64_t snap_length(int64_t S) {
-  const int64_t snap_short = S < kSnapRow ? S : kSnapRow;
+__device__ __forceinline__ uint32_t snap_length(uint32_t S) {
+  const uint32_t snap_short = S < kSnapRow ? S : kSnapRow;
   return S / 4 > snap_short ? S / 4 : snap_short;
 }
 
 template <int W>
 __device__ __forceinline__ Slice make_slice(const WalkArgs &a) {
   Slice s;
-  int64_t S, ns, items, nnz;
+  uint32_t S, ns, items, nnz;
   slice_count(a, &S, &ns, &items, &nnz);
-  constexpr int kWorkersPerWave = 64 / W;
-  const int64_t wpb = (int64_t)(blockDim.x >> 6) * kWorkersPerWave;
-  const int64_t local = (threadIdx.x >> 6) * kWorkersPerWave + (threadIdx.x & 63) / W;
+  constexpr uint32_t kWorkersPerWave = 64 / W;
+  const uint32_t wpb = (blockDim.x >> 6) * kWorkersPerWave;
+  const uint32_t local = (threadIdx.x >> 6) * kWorkersPerWave + (threadIdx.x & 63) / W;
   if (a.xcd_span > 0) {
-    const int64_t xcd = blockIdx.x % a.xcds;
-    const int64_t in_xcd = (int64_t)(blockIdx.x / a.xcds) * wpb + local;
-    const int64_t per_xcd = (ns + a.xcds - 1) / a.xcds;
-    s.id = xcd * per_xcd + in_xcd;
+    const uint32_t xcds = (uint32_t)a.xcds;
+    const uint32_t in_xcd = blockIdx.x / xcds * wpb + local;
+    const uint32_t per_xcd = (ns + xcds - 1) / xcds;
+    s.id = blockIdx.x % xcds * per_xcd + in_xcd;
     s.active = in_xcd < per_xcd && s.id < ns;
   } else {
-    s.id = (int64_t)blockIdx.x * wpb + local;
+    s.id = blockIdx.x * wpb + local;
     s.active = s.id < ns;
   }
   s.i0 = s.p0 = s.i1 = s.p1 = 0;
   s.head = false;
   if (!s.active) return s;
-  const int64_t d0 = s.id * S;
-  const int64_t d1 = d0 + S < items ? d0 + S : items;
-  mp_search2<W>(a.rowptr, a.N, nnz, d0, d1, &s.i0, &s.i1);
+  const uint32_t d0 = (uint32_t)s.id * S;
+  const uint32_t d1 = items - d0 > S ? d0 + S : items;
+  uint32_t i0, i1;
+  mp_search2<W>(a.rowptr, (uint32_t)a.N, nnz, d0, d1, &i0, &i1);
+  s.i0 = i0;
+  s.i1 = i1;
   s.p0 = d0 - s.i0;
   s.p1 = d1 - s.i1;
   // A boundary inside a short row moves back to the row's start, so only
@@ -813,7 +819,7 @@ __global__ __launch_bounds__(256) void carry_fixup(WalkArgs a, int G) {
   const int lane = threadIdx.x & 63;
   const int64_t wave = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
   const int64_t waves = (int64_t)gridDim.x * (blockDim.x >> 6);
-  int64_t S, ns, items, nnz;
+  uint32_t S, ns, items, nnz;
   slice_count(a, &S, &ns, &items, &nnz);
   // meta entries past ns belong to no slice of this call and are never read
   for (int64_t g0 = wave * G; g0 < ns; g0 += waves * G) {
