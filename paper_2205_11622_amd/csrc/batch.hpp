@@ -247,14 +247,18 @@ struct BatchWalk {
     if (!in) ws = we = 0;
   }
 
-  // The rows with nonzeros s .. e-1 in the batch [pb, pe): several(R, rb, b, s, e)
+  // The rows with nonzeros s .. e-1 in the batch [pb, pe): each(row, s, n) for NPP >= 8 rows
+  // at once, one a lane group, where the 64 rows of a window have at most four each
+  // (groups past the last row repeat it: such rows leave a pass of the whole wave
+  // mostly empty; 1M rows of 3, us: fused at 32 265 -> 219, at 16 210 -> 168, SpMM at 16
+  // 145 -> 122, SDDMM at 32 139 -> 119); else several(R, rb, b, s, e)
   // for R = 4 rows rb + b[0..3] of at most NPP nonzeros or R = 2 rows of at most
   // 2 * NPP (four passes side by side either way), one(row, s, e) for the others.
   // Rows of 10 nonzeros, one after another, would leave three of the four
   // gathers of a lane unused: in sets they run 1.2-1.4x faster at K = L = 16.
-  template <int NPP, typename One, typename Several>
+  template <int NPP, typename One, typename Several, typename Each>
   __device__ __forceinline__ void for_rows(uint32_t ib, uint32_t pb, uint32_t pe, One one,
-                                           Several several) {
+                                           Several several, Each each) {
     for (uint32_t rb = ib;; rb += 64) {
       window(rb);
       const uint32_t vs = ws > pb ? ws : pb, ve = we < pe ? we : pe;
@@ -262,6 +266,22 @@ struct BatchWalk {
       uint64_t mask = __ballot(len > 0);
       const uint64_t tall4 = __ballot(len > NPP), tall2 = __ballot(len > 2 * NPP);
       const bool more = rb + 63 < rlast && (uint32_t)__builtin_amdgcn_readlane(we, 63) < pe;
+      if constexpr (NPP >= 8) {
+        if (__popcll(mask) > 4 && __ballot(len > 4) == 0) {
+          const int count = __popcll(mask);
+          const int rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
+                                                     __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0));
+          // lane k: the lane of the window's k-th row with nonzeros
+          int nth = lane;
+          if (mask != ~0ull) nth = __builtin_amdgcn_ds_permute((len > 0 ? rank : 63) << 2, lane);
+          for (int k0 = 0; k0 < count; k0 += NPP) {
+            const int k = k0 + lane / (64 / NPP);
+            const int b = bperm_i(k < count ? k : count - 1, nth);
+            each(rb + b, (uint32_t)bperm_i(b, (int)vs), bperm_i(b, len));
+          }
+          mask = 0;
+        }
+      }
       // the next R rows, if there are that many and none is in `tall`
       auto set = [&](auto r, uint64_t tall) {
         constexpr int R = decltype(r)::value;
@@ -388,6 +408,27 @@ struct BatchWalk {
           lanes_ordered();
 #pragma unroll
           for (int u = 0; u < U; ++u) finish(c[u / S], x[u], z[u], zp[u]);
+        },
+        [&](uint32_t row, uint32_t s, int n) {
+          int2 *zp[U];
+          int2 z[U];
+          float c[4], x[U][4];
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            zp[u] = nz + ((int)(s - pb) + (u < n ? u : n - 1));
+            z[u] = *zp[u];
+          }
+          load_c(c, row);
+          bool any[U];
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            any[u] = u < 2 || __ballot(n > u) != 0;
+            if (any[u]) load_d(x[u], z[u].x);
+          }
+          lanes_ordered();
+#pragma unroll
+          for (int u = 0; u < U; ++u)
+            if (any[u]) finish(c, x[u], z[u], zp[u]);
         });
   }
 
@@ -518,6 +559,31 @@ struct BatchWalk {
               store(dst, o);
             }
           }
+        },
+        [&](uint32_t row, uint32_t s, int n) {
+          int2 z[U];
+          float x[U][4], acc[4] = {0.f, 0.f, 0.f, 0.f};
+          bool any[U];
+#pragma unroll
+          for (int u = 0; u < U; ++u) z[u] = nz[(int)(s - pb) + (u < n ? u : n - 1)];
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            any[u] = u < 2 || __ballot(n > u) != 0;
+            if (any[u]) load_e(x[u], z[u].x);
+          }
+#pragma unroll
+          for (int u = 0; u < U; ++u)
+            if (any[u] && u < n) add(acc, x[u], z[u]);
+          if (lane_in) {
+            float *dst = row_at(row) + col;
+            if (row == crow) {
+#pragma unroll
+              for (int v = 0; v < 4; ++v)
+                if (!TAIL || v < valid || a.Lw >= 4) acc[v] = dst[v] + acc[v];
+            }
+            lanes_ordered();  // groups that repeat a row, and the last lane, read what others store
+            store(dst, acc);
+          }
         });
   }
 
@@ -632,9 +698,11 @@ struct BatchWalk {
 };
 
 // Four gathers in flight per lane and six waves per SIMD; eight gathers need
-// 120 registers and leave four.
+// 120 registers and leave four.  SDDMM, with fewer registers, has seven: with six the
+// 27-point stencils take 11% longer at K = 32 (114^3 635 -> 704 us), if 25% less at 64.
 template <int MODE, bool TAIL, bool BIG>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(6))) void walk_batch(WalkArgs a) {
+__global__ __launch_bounds__(64) 
+    __attribute__((amdgpu_waves_per_eu(MODE == kSddmm ? 7 : 6))) void walk_batch(WalkArgs a) {
   __shared__ int2 nonzeros[kBatch];
   const Part s = make_part(a);
   if (!s.active) return;

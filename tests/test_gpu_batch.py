@@ -191,3 +191,44 @@ def test_nonzeros_up_to_the_index_limit(gpu):
     assert float(slnr.sparselnr_spmm(rowptr, col, Y, E)) == 30
     del col, vals, Y
     torch.cuda.empty_cache()
+
+
+# rows of at most four nonzeros, one a lane group: full and ragged groups, windows with a
+# longer row among them, rows that go on in the next batch of 512 or in the next slice
+@pytest.mark.parametrize("longest", [1, 3, 4, 5])
+@pytest.mark.parametrize("K,L", [(16, 16), (32, 32), (5, 30), (3, 2), (16, 64), (64, 16), (300, 20)])
+def test_rows_of_a_few_nonzeros(gpu, K, L, longest):
+    rng = np.random.default_rng(longest)
+    n = rng.integers(0, longest + 1, 30_011)
+    n[:130] = longest            # windows of 64 rows without an empty one
+    n[200:1000:9] = 0
+    n[2000:2063] = 0             # one row in a window, then five
+    n[2064:2128] = 0
+    n[[2064, 2070, 2071, 2100, 2127]] = longest
+    n[9000] = 700
+    p = make_problem(n, 1213, K, L, seed=K, dups=True, unsorted=True, dense="normal")
+    d = upload(p)
+    try:
+        for factor in (0, 1):
+            slnr.sparselnr_set_grid_factor(factor)
+            check_A_rows(p, fused(d), what="fused")
+            Y, A = unfused(d)
+            check_Y(p, Y)
+            check_A_rows(p, A, what="unfused")
+    finally:
+        slnr.sparselnr_set_grid_factor(0)
+
+
+def test_rows_of_a_few_nonzeros_over_batches(gpu):
+    # slices of many batches: a row is cut by every third batch's end
+    p = make_problem(np.tile([3, 0, 4, 2], 350_000), 4096, 16, 16, seed=2, dups=True)
+    d = upload(p)
+    try:
+        slnr.sparselnr_set_grid_factor(1)
+        A, (Y, Au) = fused(d), unfused(d)
+        rows = np.arange(0, p.N, 7)
+        check_A_rows(p, A, rows=rows, what="fused")
+        check_Y(p, Y, rows=rows)
+        check_A_rows(p, Au, rows=rows, what="unfused")
+    finally:
+        slnr.sparselnr_set_grid_factor(0)
