@@ -117,10 +117,10 @@ __device__ __forceinline__ int value_of(int lane) {
 }
 
 // Floats col .. col+3 of row j; of a row too narrow for that (not `wide`) only
-// the first `valid`.
+// the first `valid`.  `once`: with the nontemporal hint.
 template <bool TAIL, bool BIG>
 __device__ __forceinline__ void ld_cols(float (&r)[4], const float *base, uint32_t j, int64_t stride,
-                                        int col, bool wide, int valid) {
+                                        int col, bool wide, int valid, bool once = false) {
   const float *p;
   if constexpr (BIG) {
     p = base + (int64_t)j * stride + col;
@@ -129,7 +129,15 @@ __device__ __forceinline__ void ld_cols(float (&r)[4], const float *base, uint32
     p = reinterpret_cast<const float *>(reinterpret_cast<const char *>(base) + off);
   }
   if (!TAIL || wide) {  // uniform
-    const f4u_t x = *reinterpret_cast<const f4u_t *>(p);
+    const f4u_t *q = reinterpret_cast<const f4u_t *>(p);
+    f4u_t x;
+    if (once) {            // uniform
+      asm volatile("");    // two loads: merged into one, they lose the hint
+      x = __builtin_nontemporal_load(q);
+      asm volatile("");
+    } else {
+      x = *q;
+    }
     r[0] = x[0]; r[1] = x[1]; r[2] = x[2]; r[3] = x[3];
   } else {
     r[0] = r[1] = r[2] = r[3] = 0.f;
@@ -340,7 +348,7 @@ struct BatchWalk {
       }
     };
     auto load_c = [&](float (&c)[4], uint32_t row) {
-      ld_cols<TAIL, true>(c, a.C, row, a.K, col, a.K >= 4, valid);
+      ld_cols<TAIL, true>(c, a.C, row, a.K, col, a.K >= 4, valid, a.stream_c);
       drop_front(c);
     };
     auto load_d = [&](float (&x)[4], int j) {
@@ -432,6 +440,10 @@ struct BatchWalk {
         });
   }
 
+  __device__ __forceinline__ bool in_carry(uint32_t row) const {
+    return row == i1 || (row == i0 && head);
+  }
+
   // Where the sums of a row go (column l0 of it), also those of a first batch of it.
   __device__ __forceinline__ float *row_at(uint32_t row) const {
     return row == i1           ? tail_slot
@@ -457,11 +469,20 @@ struct BatchWalk {
     auto load_e = [&](float (&x)[4], int j) {
       ld_cols<TAIL, BIG>(x, a.E, j, a.L, a.l0 + col, a.Lw >= 4, valid);
     };
-    auto store = [&](float *dst, const float (&r)[4]) {
+    // A's rows carry the nontemporal hint, partial rows, which the fixup reads next, do
+    // not (20000 power-law rows of 20 at 64: 50 us, 57 with it).  Rows of A, us with and
+    // without: SpMM at 256 with 1M rows of 4 843 / 905, of 8 1503 / 1582.
+    auto store = [&](uint32_t row, float *dst, const float (&r)[4]) {
       if (!TAIL || a.Lw >= 4) {
         f4u_t o;
         o[0] = r[0]; o[1] = r[1]; o[2] = r[2]; o[3] = r[3];
-        *reinterpret_cast<f4u_t *>(dst) = o;
+        if (in_carry(row)) {
+          asm volatile("");  // two stores: merged into one, they lose the hint
+          *reinterpret_cast<f4u_t *>(dst) = o;
+          asm volatile("");
+        } else {
+          __builtin_nontemporal_store(o, reinterpret_cast<f4u_t *>(dst));
+        }
       } else {
 #pragma unroll
         for (int v = 0; v < 3; ++v)
@@ -524,7 +545,7 @@ struct BatchWalk {
                 if (!TAIL || v < valid || a.Lw >= 4) acc[v] = dst[v] + acc[v];
               if constexpr (TAIL) lanes_ordered();  // the last lane reads what its neighbour stores
             }
-            store(dst, acc);
+            store(row, dst, acc);
           }
         },
         [&](auto r, uint32_t rb, i4_t b, i4_t s, i4_t e) {
@@ -556,7 +577,7 @@ struct BatchWalk {
                   if (!TAIL || v < valid || a.Lw >= 4) o[v] = dst[v] + o[v];
                 if constexpr (TAIL) lanes_ordered();
               }
-              store(dst, o);
+              store(row, dst, o);
             }
           }
         },
@@ -582,7 +603,7 @@ struct BatchWalk {
                 if (!TAIL || v < valid || a.Lw >= 4) acc[v] = dst[v] + acc[v];
             }
             lanes_ordered();  // groups that repeat a row, and the last lane, read what others store
-            store(dst, acc);
+            store(row, dst, acc);
           }
         });
   }

@@ -282,6 +282,15 @@ Variant with_wide(Variant v) {
 // have no use for parts, SpMM at 256 839 / 918 and SDDMM 703 / 737.
 constexpr int64_t kFewRows = 16384;
 
+// The batch walk reads C with the nontemporal hint where a row is two lines of 128 bytes
+// and more (a line of narrower rows serves the next row too) and the cache of 256 MB
+// behind the L2s would not keep C for the next call.  us with / without: 1M rows of 3 at
+// K = L = 64 351 / 359, SDDMM at 256 681 / 714, 114^3 stencil at 64 1688 / 1728; K = 32,
+// 80^3 stencil 392 / 363, SDDMM of 1M rows of 3 152 / 137; 2^16 R-MAT vertices at 64
+// (16 MB of C) 76 / 72.
+constexpr int64_t kStreamWidth = 64;
+constexpr int64_t kStreamBytes = (int64_t)64 << 20;
+
 Variant pick_fused(int64_t N, int64_t M, int64_t K, int64_t L, bool al) {
   const int64_t gathered = 4 * M * (K + L);
   const bool gib = gathered >= ((int64_t)1 << 30);
@@ -561,6 +570,7 @@ int run_walk(Mode mode, const Variant *vs, const WalkArgs *as, int nv, hipStream
   a.xcds = kXcds;
   a.tk = v.tk;
   a.parts = g.parts;
+  a.stream_c = a.K >= kStreamWidth && a.N * a.K * 4 >= kStreamBytes;
   if (mode != kSddmm) {
     const CarrySize cs = carry_size(g, tile_w);
     void *ws = nullptr;
@@ -592,6 +602,7 @@ int run_walk(Mode mode, const Variant *vs, const WalkArgs *as, int nv, hipStream
       ak.tk = a.tk;
       ak.tl = a.tl;
       ak.parts = a.parts;
+      ak.stream_c = a.stream_c;
       const Variant &vk = k == 0 ? v : vs[k];  // v: the kernel chosen for this input
       hipLaunchKernelGGL(vk.fn, dim3(g.blocks), dim3(vk.block), vk.lds, stream, ak);
       hipError_t e = hipGetLastError();

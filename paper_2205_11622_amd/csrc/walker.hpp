@@ -89,6 +89,7 @@ struct WalkArgs {
   int32_t gate;
   int32_t tk, tl;     // batch walk: float4 columns of a tile of C / D and of E / A
   int32_t parts;      // batch walk: waves for a slice (odd)
+  int32_t stream_c;   // batch walk: C's rows carry the nontemporal hint
 };
 
 enum Gate : int { kGateNone = 0, kGateDense = 1, kGateSparse = 2 };
