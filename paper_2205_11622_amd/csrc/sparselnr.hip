@@ -570,6 +570,7 @@ int run_walk(Mode mode, const Variant *vs, const WalkArgs *as, int nv, hipStream
   a.xcds = kXcds;
   a.tk = v.tk;
   a.parts = g.parts;
+  a.enough = v.batch && v.part_rows == 0 && g.factor > 1 ? 2 * (g.workers / g.factor) : 0;
   a.stream_c = a.K >= kStreamWidth && a.N * a.K * 4 >= kStreamBytes;
   if (mode != kSddmm) {
     const CarrySize cs = carry_size(g, tile_w);
@@ -603,6 +604,7 @@ int run_walk(Mode mode, const Variant *vs, const WalkArgs *as, int nv, hipStream
       ak.tl = a.tl;
       ak.parts = a.parts;
       ak.stream_c = a.stream_c;
+      ak.enough = a.enough;
       const Variant &vk = k == 0 ? v : vs[k];  // v: the kernel chosen for this input
       hipLaunchKernelGGL(vk.fn, dim3(g.blocks), dim3(vk.block), vk.lds, stream, ak);
       hipError_t e = hipGetLastError();

@@ -90,6 +90,7 @@ struct WalkArgs {
   int32_t tk, tl;     // batch walk: float4 columns of a tile of C / D and of E / A
   int32_t parts;      // batch walk: waves for a slice (odd)
   int32_t stream_c;   // batch walk: C's rows carry the nontemporal hint
+  int32_t enough;     // batch walk: slices that fill the GPU, where more of them are short (0: off)
 };
 
 enum Gate : int { kGateNone = 0, kGateDense = 1, kGateSparse = 2 };
@@ -285,6 +286,14 @@ struct Slice {
 constexpr uint32_t kShortSlice = 16;
 constexpr uint32_t kSnapRow = 16;
 
+// The host sizes a grid of several resident ones by rows, for it does not know nnz.  The
+// batch walk's slices of rows of a few nonzeros would be short, and each costs 4 us of its
+// wave in searches and first loads; they are made up to kLongSlice items as long as
+// two resident grids of them remain.  1M rows of 3, slices of 64 / 128 / 256 items, us:
+// fused at 32 213 / 175 / 165, at 64 352 / 315 / 309, SpMM at 16 122 / 88 / 82, SDDMM at 32
+// 119 / 96 / 87; 400000 rows of 3 at 32 77 / 74 / 72.
+constexpr uint32_t kLongSlice = 256;
+
 // Slices are S = ceil(items / workers) items long, raised to min_chunk (or
 // to kShortSlice, below), so small inputs use only the first
 // ns = ceil(items / S) of them.  An input with
@@ -312,6 +321,11 @@ __device__ __forceinline__ void slice_count(const WalkArgs &a, uint32_t *S_out, 
   const uint32_t nnz = (uint32_t)a.rowptr[a.N], N = (uint32_t)a.N;
   const uint32_t items = N + nnz, workers = (uint32_t)a.workers;
   uint32_t S = (items + workers - 1) / workers;
+  if (a.enough > 0 && S < kLongSlice) {  // S items still make `enough` slices
+    const uint32_t most = (items + a.enough - 1) / (uint32_t)a.enough;
+    const uint32_t len = most < kLongSlice ? most : kLongSlice;
+    S = S > len ? S : len;
+  }
   if (S < kShortSlice && nnz <= (uint64_t)kSnapRow * N) S = kShortSlice;
   else if (S < (uint32_t)a.min_chunk) S = a.min_chunk;
   *S_out = S;

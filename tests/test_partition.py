@@ -37,11 +37,17 @@ SHORT_SLICE = 16  # kShortSlice of the kernels
 SNAP_ROW = 16     # kSnapRow of the kernels
 
 
-def slice_len(items, workers, min_chunk, short=SHORT_SLICE, N=None, nnz=None):
-    """The kernels' slice length: ceil(items / workers), raised to `short`
+LONG_SLICE = 256  # kLongSlice of the kernels
+
+
+def slice_len(items, workers, min_chunk, short=SHORT_SLICE, N=None, nnz=None, enough=0):
+    """The kernels' slice length: ceil(items / workers), raised towards LONG_SLICE
+    as long as `enough` slices remain, raised to `short`
     below it when the rows average at most SNAP_ROW nonzeros (N, nnz; None:
     they do), else to min_chunk."""
     S = -(-items // workers)
+    if enough and S < LONG_SLICE:
+        S = max(S, min(LONG_SLICE, -(-items // enough)))
     short_rows = N is None or nnz <= SNAP_ROW * N
     if S < short and short_rows:
         return short
@@ -330,3 +336,16 @@ def test_fixup_groups_visit_each_head_once(ns, workers, cus):
             g0 += waves * G
     assert np.array_equal(visits[:ns], (head[:ns] >= 0).astype(int))
     assert not visits[ns:].any()
+
+
+@pytest.mark.parametrize("enough", [1, 3, 64, 1000])
+@pytest.mark.parametrize("items", [1, 63, 1000, 5000, 300_000])
+def test_long_slices_fit_the_grid(items, enough):
+    """Raised slices are no more than the grid's workers, and raised at most to what
+    makes `enough` of them."""
+    workers = enough * 4
+    S0 = slice_len(items, workers, 64)
+    S = slice_len(items, workers, 64, enough=enough)
+    assert S >= S0 and -(-items // S) <= workers
+    assert S <= max(S0, LONG_SLICE)
+    assert S == S0 or S <= max(64, -(-items // enough))
