@@ -783,12 +783,14 @@ __device__ __forceinline__ int64_t tail_run_start(const int32_t *__restrict__ me
 // each column's sum is taken in the same order either way, so the results
 // are bit-identical).  The loads of a batch are issued together, so a row
 // split over hundreds of slices (a power-law hub row) costs a few memory
-// latencies rather than one per slice.
+// latencies rather than one per slice.  16-byte loads in batches of 4 / 8 / 16, us: 5000
+// power-law rows of 20 at K = L = 64 34.1 / 28.5 / 28.6, of 50 57 / 43 / 37, 60000 of 8
+// 54.9 / 53.7 / 55.1, 2^14 R-MAT vertices 29.7 / 29.7 / 32.2.
 template <int V>
 __device__ __forceinline__ void fix_cols(const float *__restrict__ carry, float *__restrict__ arow,
                                          int64_t Lw, int64_t first, int64_t c) {
   typedef typename std::conditional<V == 4, f4_t, float>::type vec;
-  constexpr int kBatch = V == 4 ? 4 : 16;
+  constexpr int kBatch = V == 4 ? 8 : 16;
   const int lane = threadIdx.x & 63;
   auto at = [&](int64_t slot, int64_t l) {
     return *reinterpret_cast<const vec *>(carry + slot * Lw + l);
