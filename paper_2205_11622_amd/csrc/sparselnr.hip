@@ -29,6 +29,7 @@ constexpr int kBlock = 256;       // threads per block (4 waves)
 // dispatcher a finer-grained tail and spread each XCD's share more evenly.
 constexpr int kWalkBlock = 64;
 constexpr int kMinChunk = 64;     // smallest merge-path slice per worker (see slice_count)
+constexpr int kMinShortChunk = 48;  // of the batch walk where rows are short
 constexpr int kXcds = 8;          // MI355X deals blocks over 8 XCDs
 constexpr int kGridFactor = 8;    // resident grids per walk launch for large inputs
 constexpr int kBatchTile = 64;    // batch walk: at most 64 float4 columns per tile
@@ -566,6 +567,7 @@ int run_walk(Mode mode, const Variant *vs, const WalkArgs *as, int nv, hipStream
   }
   a.workers = g.workers;
   a.min_chunk = kMinChunk;
+  a.min_short = v.batch ? kMinShortChunk : kMinChunk;
   a.xcd_span = g.xcd_span;
   a.xcds = kXcds;
   a.tk = v.tk;
@@ -594,6 +596,7 @@ int run_walk(Mode mode, const Variant *vs, const WalkArgs *as, int nv, hipStream
       WalkArgs ak = as[k];  // the shared fields come from a
       ak.workers = a.workers;
       ak.min_chunk = a.min_chunk;
+      ak.min_short = a.min_short;
       ak.xcd_span = a.xcd_span;
       ak.xcds = a.xcds;
       ak.carry = a.carry;

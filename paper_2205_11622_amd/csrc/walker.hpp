@@ -76,6 +76,7 @@ struct WalkArgs {
   int32_t Lw;         // width of that tile
   int32_t workers;    // workers in the grid
   int32_t min_chunk;  // smallest merge-path slice per worker
+  int32_t min_short;  // and where rows average at most kSnapRow nonzeros
   int32_t xcd_span;   // blocks per XCD for the XCD-contiguous remap (0: off)
   int32_t xcds;       // XCDs the hardware deals blocks across
   // consumer row width and the optional parts of the Section 6.2 benchmarks
@@ -307,8 +308,13 @@ constexpr uint32_t kLongSlice = 256;
 // 64-item slices: a hub row there would split into 4x more partial rows,
 // which one wave of the fixup sums (1000 rows with one of 10^5 nonzeros:
 // 172 us against 90 at K = L = 32).  Inputs with 16 to 64 items per worker
-// also keep 64-item slices (65536 rows of 16 nonzeros: the unfused passes
-// 1.7% slower with 34-item slices).  With the XCD
+// also keep 64-item slices in the fixed-width kernels (65536 rows of 16 nonzeros: the
+// unfused passes 1.7% slower with 34-item slices).  The batch walk, whose waves take
+// their rows one after another, has slices of 48 there if rows average at most kSnapRow
+// nonzeros (slices of 64 / 48 / 32 items, us: 20000 rows of 5 at K = L = 128 39.3 / 33.0 /
+// 29.0, 20000 of 10 at 64 29.6 / 27.5 / 25.9, SpMM of them at 64 18.4 / 18.1 / 20.3, at
+// 128 20.3 / 20.8 / 22.3, fused at 32 17.0 / 18.1 / 18.3; 5000 power-law rows of 50 at 64
+// 43 / 50 / 50).  With the XCD
 // remap, XCD x (blocks are dealt round-robin over the XCDs) takes the
 // contiguous run of slices [x * ns / xcds, (x + 1) * ns / xcds), so that the
 // workers sharing an L2 walk neighbouring rows and every XCD gets an equal
@@ -326,8 +332,10 @@ __device__ __forceinline__ void slice_count(const WalkArgs &a, uint32_t *S_out, 
     const uint32_t len = most < kLongSlice ? most : kLongSlice;
     S = S > len ? S : len;
   }
-  if (S < kShortSlice && nnz <= (uint64_t)kSnapRow * N) S = kShortSlice;
-  else if (S < (uint32_t)a.min_chunk) S = a.min_chunk;
+  const bool short_rows = nnz <= (uint64_t)kSnapRow * N;
+  const uint32_t least = short_rows ? a.min_short : a.min_chunk;
+  if (S < kShortSlice && short_rows) S = kShortSlice;
+  else if (S < least) S = least;
   *S_out = S;
   *ns_out = (items + S - 1) / S;
   *items_out = items;
