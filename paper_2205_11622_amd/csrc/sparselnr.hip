@@ -264,24 +264,30 @@ Variant with_wide(Variant v) {
   return v;
 }
 
-// The batch walk serves every width; the kernels of fixed width stay where they
-// are the faster ones (us on MI355X, fixed width / batch):
-//  * K = L = 64 and 128 with at least 1 GiB of D and E rows, 64-lane workers.
-//    R-MAT graphs: 2^22 vertices at 64 10617 / 11463, 2^21 at 64 3136 / 3449,
-//    2^20 at 128 2436 / 2566 to 2674 / 2896 by box: their hot columns crowd a few
-//    memory channels, and one gather in flight per wave crowds them least.  (Other
-//    matrices of that size lose by it: 3M uniform rows of 16 at 64 5296 / 4491.)
-//    Below 1 GiB the batch walk is ahead on all: 2^19 vertices at 64 598 / 479, 2^18
-//    at 128 582 / 520, 700001 power-law rows at 128 2508 / 2010.
-//  * widths of 512 (two tiles of the batch walk, one after the other) with few
-//    rows a wave: 3000 power-law rows of 20 at K = L = 512 54 / 63, 2^13 R-MAT
-//    vertices SDDMM 24 / 36; 46656 rows 487 / 408.
-// At K = L = 256, K = 16 with L = 256 and 256 alone the parts of the batch walk's
-// slices (make_grid) put it ahead: 27-point stencil of 101^3 at K = L = 256
-// 6100 / 4055, of 128^3 at 16, 256 5883 / 4740, SpMM at 256 of 101^3 3200 / 2163, of
-// 36^3 84 / 75; R-MAT and power-law graphs within 1%; rows of 3 or 4 nonzeros, which
-// have no use for parts, SpMM at 256 839 / 918 and SDDMM 703 / 737.
-constexpr int64_t kFewRows = 16384;
+// The batch walk serves every width; kernels of fixed width stay for two kinds of calls
+// (us on MI355X, fixed width / batch walk):
+//  * K = L = 64 and 128 with at least 1 GiB of D and E rows, 64-lane workers: R-MAT
+//    graphs, whose hot columns crowd a few memory channels, which one gather in flight a
+//    wave crowds least.  Vertices, edges a vertex: 128 columns 2^20, 4 857 / 945, 8 1524 /
+//    1647, 16 2830 / 2979; 2^21, 4 1744 / 1908, 8 3146 / 3402, 16 5853 / 6117; 64 columns
+//    2^21, 16 2785 / 2987; 2^22, 4 1766 / 1916, 16 5963 / 6452, 32 11376 / 12344.  Below 1 GiB
+//    they draw level: 128 columns 2^19, 8 661 / 667, 16 1160 / 1217 (on another card 1127 /
+//    1094), 2^18, 16 563 / 481; 64 columns 2^20, 8 690 / 674, 16 1174 / 1217, 2^19, 16 595 /
+//    481.  Any other matrix of 1 GiB and more would be faster with the batch walk, and the
+//    host sees sizes only: power-law rows 1.05M at 128 2477 / 2049, 2.5M at 64 2162 / 1817,
+//    uniform 1.05M at 128 2663 / 2303, 2.5M at 64 2338 / 2009, 27-point stencils 110^3 at 128
+//    5127 / 2613, 128^3 at 64 3682 / 2165.
+//  * widths of 512 (two tiles of the batch walk, one after the other) with a row or less
+//    for each resident wave.  Fused, power-law rows of 20: 2000 rows 44 / 60, 4000 64 / 78,
+//    8000 95 / 96, 16000 184 / 174; SDDMM 4000 25 / 30, 8000 38 / 38, 16000 78 / 75; SpMM 4000
+//    46 / 50, 8000 58 / 56; uniform rows of 8 4000 23 / 24, 8000 46 / 42; stencils 25^3 166 /
+//    99, 32^3 430 / 218.
+// At 256 columns the parts of the batch walk's slices (make_grid) put it ahead of the
+// kernels it replaced: stencils 101^3 at K = L = 256 6210 / 4057, 128^3 at K = 16, L = 256
+// 5877 / 4689, SpMM at 256 of 101^3 3231 / 2088; 300000 power-law rows 1413 / 1373; 2^18
+// R-MAT vertices 1268 / 1278 and 1434 / 1196 by card; 1M rows of 4, SpMM 839 / 846, of 3,
+// SDDMM 694 / 681.
+constexpr int64_t kFewRows = 6144;
 
 // The batch walk reads C with the nontemporal hint where a row is two lines of 128 bytes
 // and more (a line of narrower rows serves the next row too) and the cache of 256 MB
@@ -437,11 +443,14 @@ int blocks_per_cu(int dev, KernelFn fn, int block, size_t lds, int *out) {
 // (make_part): the rows that the waves of an XCD walk at one moment are then so few
 // that the D and E rows which neighbouring rows share stay in its 4 MB of L2, and the
 // parts need no carry.  Parts of 3 rows from 256 floats a nonzero on, of 6 where one
-// of the two rows has 96 (us, whole slices / parts, 27-point stencils: K = L = 128 of
-// 101^3 2757 / 2040, SpMM at 128 1854 / 1015, K = 16, L = 256 of 128^3 6441 / 4740);
-// narrower rows fit as they are (K = L = 64 of 101^3 1066 / 1134).  The device makes
-// fewer of them where rows are short (kPartItems); the waves left over end at once,
-// at 4.5 a ns: 1M uniform rows of 4 at K = L = 128 920 / 968, of 16 2744 / 2870.  The number is odd: with 2, 4 or 8
+// of the two rows has 96.  us, whole slices / parts of 6 / of 3:
+//   100^3 stencil  SpMM at 80 1051 / 755 / 852, 96 1283 / 808 / 885, 128 1731 / 1078 / 1001;
+//                  fused at 64 1328 / 1113 / 1212, 96 2636 / 1539 / 1607, 128 3637 / 2221 / 1879
+//   1M rows of 5   SpMM at 64 225 / 258 / 283, 80 423 / 465 / 490, 96 459 / 501 / 524, 128 522 /
+//                  565 / 586;  600000 rows of 16 fused at 64 714 / 721 / 725, 128 1411 / 1418 / 1464
+// so the line at 96 is where stencils gain most of their time for the tenth that rows
+// of a few nonzeros lose to the waves left over (the device makes fewer parts where rows
+// are short, kPartItems) and to each part's start.  The number is odd: with 2, 4 or 8
 // parts the last one of each slice, which has the ends of long rows, would always
 // meet the same shader engines (2^19 R-MAT vertices at 64: 4 parts 847, 5 514).
 Grid make_grid(int cus, int per_cu, int block, int W, int64_t N, int factor = 0, int rows = 0,
