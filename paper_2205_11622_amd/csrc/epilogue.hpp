@@ -64,7 +64,7 @@ __global__ __launch_bounds__(WL ? 1024 : 256) void walk_epi(WalkArgs a) {
   }
   const Slice s = make_slice<W>(a);
   const int64_t worker = s.id;
-  RowWalk<MODE, W, 1, KV, LV, SCHED, U, HAD> rw(a, s.p1, (uint32_t)LIN * 4u);
+  RowWalk<MODE, W, KV, LV, SCHED, U, HAD> rw(a, s.p1, (uint32_t)LIN * 4u);
   const int32_t *__restrict__ rowptr = a.rowptr;
   const float *__restrict__ Cm = a.C;
   const float *__restrict__ Wm = a.Wep;

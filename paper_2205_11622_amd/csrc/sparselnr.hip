@@ -166,10 +166,10 @@ struct Variant {
   int part_rows = 0;      // rows per part of a slice (0: slices are not parted)
 };
 
-template <int MODE, int W, int NB, int KV, int LV, int SCHED = slnr::kPipelined, int U = 1>
+template <int MODE, int W, int KV, int LV, int SCHED = slnr::kPipelined, int U = 1>
 Variant fast() {
   Variant v;
-  v.fn = slnr::walk_fast<MODE, W, NB, KV, LV, SCHED, U>;
+  v.fn = slnr::walk_fast<MODE, W, KV, LV, SCHED, U>;
   v.W = W;
   v.batch = false;
   v.block = kWalkBlock;
@@ -259,7 +259,7 @@ constexpr int kPU128W = 10;
 // 35-55% slower (4x fewer workers).
 template <int MODE, int KV, int LV, int SCHED, int U>
 Variant with_wide(Variant v) {
-  v.fn_wide = slnr::walk_fast<MODE, 64, 1, KV, LV, SCHED, U>;
+  v.fn_wide = slnr::walk_fast<MODE, 64, KV, LV, SCHED, U>;
   v.W_wide = 64;
   return v;
 }
@@ -303,21 +303,21 @@ Variant pick_fused(int64_t N, int64_t M, int64_t K, int64_t L, bool al) {
   const bool gib = gathered >= ((int64_t)1 << 30);
   if (al) {
     if (gib && K == 64 && L == 64)
-      return with_wide<kFused, 1, 1, kFS, kPU>(fast<kFused, 16, 1, 4, 4, kFS, kPU>());
+      return with_wide<kFused, 1, 1, kFS, kPU>(fast<kFused, 16, 4, 4, kFS, kPU>());
     if (gib && K == 128 && L == 128)
-      return with_wide<kFused, 2, 2, kFS, kPU128W>(fast<kFused, 32, 1, 4, 4, kFS, kPU128>());
-    if (N <= kFewRows && K == 512 && L == 512) return fast<kFused, 64, 1, 8, 8, kFS, kPU>();
+      return with_wide<kFused, 2, 2, kFS, kPU128W>(fast<kFused, 32, 4, 4, kFS, kPU128>());
+    if (N <= kFewRows && K == 512 && L == 512) return fast<kFused, 64, 8, 8, kFS, kPU>();
   }
   return batch<kFused>(M, K, L);
 }
 
 Variant pick_sddmm(int64_t N, int64_t M, int64_t K, bool al) {
-  if (al && K == 512 && N <= kFewRows) return fast<kSddmm, 64, 1, 8, 4, kUS, kPU>();
+  if (al && K == 512 && N <= kFewRows) return fast<kSddmm, 64, 8, 4, kUS, kPU>();
   return batch<kSddmm>(M, K, 0);
 }
 
 Variant pick_spmm(int64_t N, int64_t M, int64_t L, bool al) {
-  if (al && L == 512 && N <= kFewRows) return fast<kSpmm, 64, 1, 4, 8, kUS, kPU>();
+  if (al && L == 512 && N <= kFewRows) return fast<kSpmm, 64, 4, 8, kUS, kPU>();
   return batch<kSpmm>(M, 0, L);
 }
 

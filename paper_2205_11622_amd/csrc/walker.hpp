@@ -17,11 +17,12 @@
 // swizzle, then the consumer (SpMM inner l-loop) adds y * E_j into the row
 // accumulators, also in registers.  The scalar temporary is the one the
 // paper's Algorithm 1 derives for this expression (Section 4.2: no index
-// below the nest boundary is shared, so the temporary is a scalar).  The
-// producer and consumer may use different lane mappings inside one row, the
-// GPU reading of the branched iteration graph (Section 4.1): with K = 16 and
-// L = 256, 4-lane groups compute 16 scalars at once and the whole wave then
-// streams each 1 KB row of E.
+// below the nest boundary is shared, so the temporary is a scalar).  This
+// file has the work split, the walk of fixed widths (K and L a multiple of the
+// worker's lanes) and the carry fixup; batch.hpp has the walk of any widths,
+// whose producer and consumer take different lane mappings, the GPU reading
+// of the branched iteration graph (Section 4.1), and epilogue.hpp the products
+// with a dense matrix.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -46,11 +47,7 @@ enum Mode : int { kFused = 0, kSddmm = 1, kSpmm = 2 };
 //              row has arrived, then all arithmetic.  Fewer requests in
 //              flight per worker keeps workers of an XCD in step, which keeps
 //              rows shared by neighbouring rows (banded matrices) in L2.
-//  kBurst      all index broadcasts of the step, then all of its gathers at
-//              once, then all arithmetic: one memory latency per step.  For
-//              inputs too small to fill the GPU, whose time is the chain of
-//              dependent loads of one worker, not the traffic.
-enum Sched : int { kPipelined = 0, kPaced = 1, kBurst = 2 };
+enum Sched : int { kPipelined = 0, kPaced = 1 };
 
 // s_waitcnt immediate (gfx9 encoding) waiting for vmcnt <= V only.
 template <int V>
@@ -410,10 +407,9 @@ struct Gather {
 //
 // The nonzero loop of one row inside one slice, shared by the walk kernels.
 // W   lanes per worker (4..64); the consumer spreads E_j / A_i over them.
-// NB  nonzeros per producer pass; PS = W / NB lanes form one dot product.
-// KV  floats of C_i / D_j per producer lane (K = PS * KV).
+// KV  floats of C_i / D_j per lane (K = W * KV).
 // LV  floats of E_j / A_i per lane (L = W * LV).
-// SCHED, U  gather schedule and, for kPaced and kBurst, the nonzeros per step.
+// SCHED, U  gather schedule and, for kPaced, the nonzeros per step.
 // HAD  the consumer row is E_j .* G2_j (Hadamard product of two gathers).
 //
 // The state is group-uniform (all W lanes agree on p, n), so lane-group
@@ -427,15 +423,11 @@ struct Gather {
 // compared in one process), and slower for the wider rows of rmat1m and
 // the stencil.
 
-template <int MODE, int W, int NB, int KV, int LV, int SCHED, int U, int HAD = 0>
+template <int MODE, int W, int KV, int LV, int SCHED, int U, int HAD = 0>
 struct RowWalk {
-  static constexpr int PS = W / NB;
   static_assert(W >= 4 && W <= 64 && (W & (W - 1)) == 0, "W");
-  static_assert(NB >= 1 && W % NB == 0, "NB");
-  static_assert(SCHED == kPipelined || (U >= 1 && U <= W && (NB == 1 || U == NB)), "U");
-  static_assert(SCHED != kBurst || NB == 1, "burst steps are built for one dot per pass");
-  static constexpr bool kStep = SCHED == kPaced || SCHED == kBurst;
-  static_assert(!HAD || (NB == 1 && MODE == kSpmm), "Hadamard rows come with the one-dot SpMM");
+  static_assert(SCHED == kPipelined || (U >= 1 && U <= W), "U");
+  static_assert(!HAD || MODE == kSpmm, "Hadamard rows come with the SpMM");
 
   const int32_t *__restrict__ colidx;
   const float *__restrict__ vals;
@@ -445,28 +437,19 @@ struct RowWalk {
   float *__restrict__ out;  // SDDMM values (kSddmm)
   int64_t p1;               // end of the slice's nonzeros
   uint32_t strideD, strideE, offD, offE;  // row strides and this lane's offset, in bytes
-  int glane, gbase, q, sub;
+  int glane, gbase;
   int64_t wb;  // nonzero window: wj = colidx[wb + glane], wv = vals[wb + glane]
   int wj;
   float wv;
-  // multi-dot SDDMM passes: this lane's slice of the D row of the next
-  // pass's nonzero, gathered one pass ahead.  (In the fused walk the same
-  // prefetch gains nothing at its best grid factor on the 27-point stencil,
-  // and its 8 extra registers cost a wave per SIMD, so the fused passes
-  // gather their own D rows.)
-  float dnext[KV];
-  int64_t pnext;  // first nonzero of the pass dnext belongs to (never a p otherwise)
 
   __device__ __forceinline__ RowWalk(const WalkArgs &a, int64_t p1_, uint32_t strideE_)
       : colidx(a.colidx), vals(a.vals), Dm(a.D), Em(a.E), Gm(a.G2), out(a.out), p1(p1_),
         strideD((uint32_t)a.K * 4u), strideE(strideE_), wb(-((int64_t)1 << 40)), wj(0),
-        wv(0.f), pnext(-((int64_t)1 << 40)) {
+        wv(0.f) {
     const int lane = threadIdx.x & 63;
     glane = lane & (W - 1);
     gbase = lane - glane;
-    q = glane % PS;    // k-slice of this lane in its dot product
-    sub = glane / PS;  // which nonzero of a producer pass (NB > 1)
-    offD = (uint32_t)(q * KV) * 4u;
+    offD = (uint32_t)(glane * KV) * 4u;
     offE = (uint32_t)(glane * LV) * 4u;
   }
 
@@ -483,13 +466,11 @@ struct RowWalk {
             wv = kNT ? ld_stream(vals + pw) : vals[pw];
           }
         }
-        // this step: the row's nonzeros inside the window (at most NB for a
-        // producer pass of the multi-dot variant)
+        // this step: the row's nonzeros inside the window
         int n = (int)(r_end - p < wb + W - p ? r_end - p : wb + W - p);
-        if (NB > 1 && n > NB) n = NB;
-        if (kStep && n > U) n = U;
+        if (SCHED == kPaced && n > U) n = U;
         const int off = (int)(p - wb);
-        if constexpr (NB == 1 && kStep) {
+        if constexpr (SCHED == kPaced) {
           uint32_t jj[U];
           float bb[U];
   #pragma unroll
@@ -504,7 +485,7 @@ struct RowWalk {
   #pragma unroll
           for (int u = 0; u < U; ++u) {
             if (u < n) {
-              if (SCHED == kPaced && u > 0) wait_vmcnt<1>();
+              if (u > 0) wait_vmcnt<1>();
               if constexpr (MODE != kSpmm) ldv_off<KV>(dr[u], Dm, jj[u] * strideD + offD);
               if constexpr (MODE != kSddmm) ldv_off<LV>(er[u], Em, jj[u] * strideE + offE);
               if constexpr (HAD) ldv_off<LV>(hr[u], Gm, jj[u] * strideE + offE);
@@ -536,7 +517,7 @@ struct RowWalk {
             }
           }
           if (MODE == kSddmm && glane < n) out[p + glane] = ysel;
-        } else if constexpr (NB == 1) {
+        } else {
           // Depth-2 software pipeline: the gathers of nonzero u are in flight
           // while nonzero u-1 is reduced and applied.  The loop body is
           // straight-line, so the wait before each consume covers exactly the
@@ -588,109 +569,6 @@ struct RowWalk {
             consume(ga, u - 1);
           }
           if (MODE == kSddmm && glane < n) out[p + glane] = ysel;
-        } else {
-          // one producer pass: sub-group `sub` forms the scalar of nonzero p+sub
-          const bool act = sub < n;
-          float y = 0.f;
-          if (MODE != kSpmm) {
-            // (lanes with sub >= n read a stale window entry and discard it)
-            const int src = (gbase + off + sub) & 63;
-            const uint32_t js = (uint32_t)bperm_i(src, wj);
-            const float bs = bperm_f(src, wv);
-            if constexpr (MODE == kSddmm) {
-              // the D rows of this pass, unless the previous pass gathered them
-              if (p != pnext && act) ldv_off<KV>(dnext, Dm, js * strideD + offD);
-              float t = 0.f;
-              if (act) {
-  #pragma unroll
-                for (int v = 0; v < KV; ++v) t = fmaf(c[v], dnext[v], t);
-              }
-              t = group_sum<PS>(t);
-              y = bs * t;
-              if (act && q == 0) out[p + sub] = y;
-              // Gather the next pass's D rows before this pass's loop
-              // overhead and store.  The next pass starts at p + n and takes
-              // at most NB nonzeros, none past the window or the slice (it
-              // may belong to the next row: its dot waits for that row's C_i,
-              // not for D).  If the window ends here, the next pass refills
-              // it and gathers its own rows.
-              const int64_t pn = p + n;
-              const int offn = (int)(pn - wb) + sub;
-              const uint32_t jn = (uint32_t)bperm_i((gbase + offn) & 63, wj);
-              if (pn - wb < W) {
-                pnext = pn;
-                if (offn < W && pn + sub < p1) ldv_off<KV>(dnext, Dm, jn * strideD + offD);
-              } else {
-                pnext = -((int64_t)1 << 40);
-              }
-            } else {
-              float dr[KV];
-              float t = 0.f;
-              if (act) {
-                ldv_off<KV>(dr, Dm, js * strideD + offD);
-  #pragma unroll
-                for (int v = 0; v < KV; ++v) t = fmaf(c[v], dr[v], t);
-              }
-              t = group_sum<PS>(t);
-              y = bs * t;
-            }
-          }
-          if (MODE != kSddmm && SCHED == kPaced) {
-            // consumer: the whole worker streams each E row, one row issued
-            // after the previous one has arrived
-            uint32_t jj[NB];
-            float yy[NB];
-  #pragma unroll
-            for (int u = 0; u < NB; ++u) {
-              const int src = (gbase + off + u) & 63;
-              jj[u] = (uint32_t)bperm_i(src, wj);
-              yy[u] = (MODE == kSpmm) ? bperm_f(src, wv) : bperm_f((gbase + u * PS) & 63, y);
-            }
-            float er[NB][LV];
-  #pragma unroll
-            for (int u = 0; u < NB; ++u) {
-              if (u < n) {
-                if (u > 0) wait_vmcnt<1>();
-                ldv_off<LV>(er[u], Em, jj[u] * strideE + offE);
-              }
-            }
-  #pragma unroll
-            for (int u = 0; u < NB; ++u) {
-              if (u < n) {
-  #pragma unroll
-                for (int v = 0; v < LV; ++v) acc[v] = fmaf(yy[u], er[u][v], acc[v]);
-              }
-            }
-          } else if (MODE != kSddmm) {
-            // consumer: the whole worker streams each E row, depth-2 pipeline
-            float ea[LV], eb[LV];
-            float ya = 0.f, yb = 0.f;
-            auto issue = [&](float (&e)[LV], float &yv, int u) {
-              const int src = gbase + off + u;
-              const uint32_t j = (uint32_t)bperm_i(src, wj);
-              yv = (MODE == kSpmm) ? bperm_f(src, wv) : bperm_f(gbase + u * PS, y);
-              ldv_off<LV>(e, Em, j * strideE + offE);
-            };
-            auto consume = [&](const float (&e)[LV], float yv) {
-  #pragma unroll
-              for (int v = 0; v < LV; ++v) acc[v] = fmaf(yv, e[v], acc[v]);
-            };
-            issue(ea, ya, 0);
-            int u = 1;
-            for (; u + 1 < n; u += 2) {
-              issue(eb, yb, u);
-              consume(ea, ya);
-              issue(ea, ya, u + 1);
-              consume(eb, yb);
-            }
-            if (u < n) {
-              issue(eb, yb, u);
-              consume(ea, ya);
-              consume(eb, yb);
-            } else {
-              consume(ea, ya);
-            }
-          }
         }
         p += n;
       }
@@ -705,11 +583,11 @@ struct RowWalk {
 // window (one row end per lane) keeps the row ends off the critical path.
 // C_i, the CSR arrays and A are streamed once per call and carry the
 // nontemporal hint.
-template <int MODE, int W, int NB, int KV, int LV, int SCHED, int U>
+template <int MODE, int W, int KV, int LV, int SCHED, int U>
 __global__ __launch_bounds__(256) void walk_fast(WalkArgs a) {
   const Slice s = make_slice<W>(a);
   if (!s.active) return;
-  RowWalk<MODE, W, NB, KV, LV, SCHED, U> rw(a, s.p1, (uint32_t)a.L * 4u);
+  RowWalk<MODE, W, KV, LV, SCHED, U> rw(a, s.p1, (uint32_t)a.L * 4u);
   const int glane = rw.glane, gbase = rw.gbase;
   const int64_t worker = s.id;  // carry slots and metadata are per slice
   int32_t *meta = a.meta + 2 * worker;
@@ -739,7 +617,7 @@ __global__ __launch_bounds__(256) void walk_fast(WalkArgs a) {
     float c[KV];
 #pragma unroll
     for (int v = 0; v < KV; ++v) c[v] = 0.f;
-    if (MODE != kSpmm && p < r_end) ldv<KV, kNT>(c, Cm + i * K + rw.q * KV);
+    if (MODE != kSpmm && p < r_end) ldv<KV, kNT>(c, Cm + i * K + rw.glane * KV);
     rw.row(p, r_end, c, acc);
     if constexpr (MODE != kSddmm) {
       if (!has_end) stv<LV>(a.carry + (worker * 2 + 1) * (int64_t)a.Lw + glane * LV, acc);
