@@ -1,7 +1,7 @@
-"""The batch walk (widths without a variant of their own, operands off 16
-bytes) at the edges of its lane counts and tiles, with rows that cross
-batches and slices, and with more columns than its 24-bit row offsets hold.
-Same rule as tests/parity.py."""
+"""The batch walk (nearly every width, any alignment) at the edges of its lane
+counts and tiles, with rows that cross batches and slices, with infinities, with
+more columns than its 24-bit row offsets hold and up to the limits of its counters;
+the sizes at which fixed-width kernels take over.  Same rule as tests/parity.py."""
 import numpy as np
 import pytest
 
@@ -76,13 +76,12 @@ def test_more_columns_than_24_bits(gpu):
     run_large(gpu, 300, 20, (1 << 24) + 77, 3, 5)
 
 
-# the sizes from which widths of 64, 128 and 256 keep kernels of their own, and
-# one column below them
-@pytest.mark.parametrize("K,L,M", [(64, 64, 1 << 21), (64, 64, (1 << 21) - 1), (128, 128, 1 << 20),
-                                   (128, 128, (1 << 20) - 1), (256, 256, (1 << 17) + 1),
-                                   (256, 256, 1 << 17), (16, 256, 246724), (16, 256, 246723)])
-def test_kernels_chosen_by_size(gpu, K, L, M):
-    run_large(gpu, 3000, 21, M, K, L)
+# the sizes from which K = L = 64 and 128 keep kernels of their own and one column below
+# them, and the rows up to which 512 columns do and one row above them
+@pytest.mark.parametrize("K,L,M,N", [(64, 64, 1 << 21, 3000), (64, 64, (1 << 21) - 1, 3000), (128, 128, 1 << 20, 3000),
+                                     (128, 128, (1 << 20) - 1, 3000), (512, 512, 5000, 6144), (512, 512, 5000, 6145)])
+def test_kernels_chosen_by_size(gpu, K, L, M, N):
+    run_large(gpu, N, 21, M, K, L)
 
 
 # wide rows, whose slices several waves share: three and five parts, hub rows over

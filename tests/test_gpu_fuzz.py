@@ -3,8 +3,7 @@
 Row counts from 1 to a few thousand (around the 64-lane window and the
 merge-path slice sizes), row-length mixes with empty rows, a single heavy
 row split over many workers, constant tiny rows, duplicate and unsorted
-columns, every width with a fast variant plus odd widths for the generic
-path, and any output width for the Section 6.2 products; the <SDDMM, SpMM>
+columns, powers of two and odd widths, and any output width for the Section 6.2 products; the <SDDMM, SpMM>
 and Section 6.2 cases run again at a seeded grid factor.  Same tolerance rule as
 tests/parity.py."""
 import numpy as np

@@ -20,9 +20,8 @@ pytestmark = pytest.mark.gpu
 
 # ---------------------------------------------------------------- variants
 
-# (K, L): the first five have hand-tuned fast variants, the rest go through
-# the generic kernel (odd widths, K != L, tiny widths, wide L needing tiles);
-# the unfused SpMM also has fast variants at L = 16 and 512.
+# (K, L): widths of the workloads, then odd widths, K != L, tiny widths, wide L needing
+# tiles.  At this size all of them go through the batch walk, except the SpMM at L = 512.
 WIDTHS = [(32, 32), (64, 64), (128, 128), (256, 256), (16, 256),
           (1, 1), (3, 5), (16, 16), (20, 36), (17, 300), (64, 520), (128, 64), (64, 512)]
 
@@ -96,8 +95,8 @@ WIDTHS = [16, 32, 64, 128, 256, 512]
 @pytest.mark.parametrize("K", WIDTHS)
 @pytest.mark.parametrize("L", WIDTHS)
 def test_fused_every_width_pair(gpu, K, L):
-    # every K, L pair of the fast variants (and the few that fall back to the
-    # generic kernel): power-law rows, one 9000-nonzero row split over many
+    # the lane counts of the batch walk in every combination, and the fixed-width
+    # kernels of 512 columns: power-law rows, one 9000-nonzero row split over many
     # workers, 30% empty rows
     n = power_law_lengths(2300, seed=K * 7 + L, cap=2000)
     n[11] = 9000
@@ -109,10 +108,12 @@ def test_fused_every_width_pair(gpu, K, L):
     check_A_rows(p, Au)
 
 
-def _large_problem(N, K, L, seed):
-    """Enough rows for several resident grids (the wide-worker kernels): Pareto
+def _large_problem(N, K, L, seed, M=None):
+    """Enough rows for several resident grids: Pareto
     row lengths with 30% empty rows and one 20000-nonzero row, built without a
-    per-row loop; columns sorted within rows, repeats allowed."""
+    per-row loop; columns sorted within rows, repeats allowed.  M: columns (N), D and E
+    then made on the GPU."""
+    M = M or N
     rng = np.random.default_rng(seed)
     lengths = power_law_lengths(N, seed=seed, scale=2.0, cap=3000)
     lengths[N // 3] = 20_000
@@ -120,27 +121,46 @@ def _large_problem(N, K, L, seed):
     rowptr[1:] = np.cumsum(lengths)
     nnz = int(rowptr[-1])
     rows = np.repeat(np.arange(N), lengths)
-    cols = rng.integers(0, N, size=nnz)
+    cols = rng.integers(0, M, size=nnz)
     order = np.lexsort((cols, rows))
     colidx = cols[order].astype(np.int32)
     vals = synth.uniform(seed, synth.STREAM_VALS, nnz, -1.0, 1.0)
     C = synth.normal(seed, synth.STREAM_C, (N, K))
-    D = synth.normal(seed, synth.STREAM_D, (N, K))
-    E = synth.normal(seed, synth.STREAM_E, (N, L))
-    return synth.Problem("large", N, N, K, L, rowptr.astype(np.int32), colidx, vals, C, D, E)
+    if M == N:
+        D = synth.normal(seed, synth.STREAM_D, (N, K))
+        E = synth.normal(seed, synth.STREAM_E, (N, L))
+    else:
+        import torch
+        g = torch.Generator(device="cuda").manual_seed(seed)
+        D, E = (torch.randn(M, w, device="cuda", generator=g).cpu().numpy() for w in (K, L))
+    return synth.Problem("large", N, M, K, L, rowptr.astype(np.int32), colidx, vals, C, D, E)
+
+
+ONE_GIB = {64: 1 << 21, 128: 1 << 20}  # columns from which D and E take 1 GiB at K = L
 
 
 @pytest.mark.parametrize("K,L", [(64, 64), (128, 128)])
 def test_large_input_wide_workers(gpu, K, L):
-    # 300000 rows need several resident grids at these widths, so the fused
-    # kernel and both unfused passes run with one 64-lane worker per wave;
-    # every row and every SDDMM value is checked, and a second call must give
-    # the same bits
-    p = _large_problem(300_000, K, L, seed=K)
+    # 300000 rows need several resident grids at these widths and D and E take 1 GiB,
+    # so the fused kernel runs with one 64-lane worker per wave, and at one grid with
+    # narrow workers; every row and every SDDMM value is checked, a second call and the
+    # no-allocation call must give the same bits
+    import torch
+    p = _large_problem(300_000, K, L, seed=K, M=ONE_GIB[K])
     d = upload(p)
     A = fused(d)
     check_A_rows(p, A, what="fused A")
     assert bool((fused(d) == A).all()), "fused result not deterministic"
+    A2 = torch.full_like(A, float("nan"))
+    slnr.sparselnr_fused_sddmm_spmm_noalloc(*(d[k] for k in ("rowptr", "colidx", "vals", "C", "D", "E")), A2)
+    assert torch.equal(A2, A), "the no-allocation call differs"
+    rows = sample_rows(p, n_random=20_000)
+    try:
+        for f in (1, 8):
+            slnr.sparselnr_set_grid_factor(f)
+            check_A_rows(p, fused(d), rows=rows, what="fused A, grid factor %d" % f)
+    finally:
+        slnr.sparselnr_set_grid_factor(0)
     Y, Au = unfused(d)
     check_Y(p, Y)
     check_A_rows(p, Au, what="unfused A")
@@ -148,12 +168,12 @@ def test_large_input_wide_workers(gpu, K, L):
 
 @pytest.mark.parametrize("K,L", [(64, 64), (128, 128)])
 def test_large_input_wide_workers_unsorted(gpu, K, L):
-    # the wide kernels on columns that are neither sorted nor distinct within
+    # the wide fused kernels on columns that are neither sorted nor distinct within
     # rows (duplicates add), and the SpMM entry point on its own; all rows
     # of a 320000-row input (above the large-input size at every kernel's
     # occupancy) are checked
     rng = np.random.default_rng(K + 1)
-    p = _large_problem(320_000, K, L, seed=K + 7)
+    p = _large_problem(320_000, K, L, seed=K + 7, M=ONE_GIB[K])
     for i in rng.choice(p.N, size=3000, replace=False):  # shuffle some rows' columns
         a, b = int(p.rowptr[i]), int(p.rowptr[i + 1])
         if b - a > 1:
@@ -200,7 +220,7 @@ def test_grid_factors(gpu, K, L):
 @pytest.mark.slow
 def test_gathered_array_above_4gib(gpu):
     # E holds M x 256 floats with M * 256 * 4 > 2^32 bytes: the gathers need
-    # 64-bit offsets, so every entry point takes the generic kernel.  Columns
+    # 64-bit offsets, so every entry point takes the batch walk that has them.  Columns
     # reach the last rows of E, and one row is split over many workers.
     K, L = 16, 256
     M = (1 << 32) // (4 * L) + 4096
@@ -284,12 +304,9 @@ def test_deterministic_bit_exact(gpu):
 def test_short_rows_of_small_inputs_are_never_split(gpu, K, L, factors):
     """An input with fewer than 16 merge-path items per worker takes 16-item
     slices, and no slice boundary splits a row of at most 16 nonzeros: every
-    row is summed by one worker in nonzero order whatever the grid factor, so
-    the factors that launch the same lane mapping give bit-identical A (and
-    every factor matches the oracle).  At K = L = 32 every factor keeps the
-    8-lane mapping (the burst walk at one resident grid, the paced one
-    above); at K = L = 64 one resident grid takes 16-lane workers and more
-    take 64-lane ones."""
+    row is summed by one wave of the batch walk, in the order that its length
+    gives, whatever the grid factor, so the factors give bit-identical A (and
+    every factor matches the oracle)."""
     rng = np.random.default_rng(41 + K)
     lengths = rng.integers(0, 17, size=3000)
     p = make_problem(lengths, 2500, K, L, seed=43 + K)
@@ -480,7 +497,7 @@ def test_config_every_row(gpu, name):
     Y = torch.empty(p.nnz, dtype=torch.float32, device=gpu)
     args = (d["rowptr"], d["colidx"], d["vals"], d["C"], d["D"], d["E"])
     try:
-        for f in (0,) + tuple(bench.GRID_FACTORS):
+        for f in bench.GRID_FACTORS:
             slnr.sparselnr_set_grid_factor(f)
             what = "%s, grid factor %s" % (name, f or "automatic")
             for t in (A, Au, Y):

@@ -52,8 +52,8 @@ def check(p, d, stream, gpu, exact):
 def test_noalloc_matches_the_fused_entry_point(gpu):
     import torch
     s = torch.cuda.Stream()
-    # a large power-law input (several resident grids, 64-lane workers, rows
-    # split over many workers), then a smaller one on the same array
+    # a large power-law input (several resident grids, rows split over many
+    # workers), then a smaller one on the same array
     big = power_law_lengths(300_000, seed=41, cap=20_000)
     big[11] = 60_000
     p1 = make_problem(big, 200_000, 128, 128, seed=41, dense="normal")
