@@ -7,7 +7,7 @@ One step is one library call over the whole matrix (merge-path walk kernel +
 carry fixup kernel), inputs resident in HBM.  Before the timed region the
 library's grid factor (resident grids per walk launch) is chosen per call:
 the timed call and each pass of the comparison run at the fastest of a fixed
-candidate list (--grid-factor / --compare-grid-factor fix them instead).  The default is
+candidate list, the library's automatic choice among them (--grid-factor / --compare-grid-factor fix them instead).  The default is
 sparselnr_fused_sddmm_spmm on the R-MAT graph with 2^20 vertices, 16 edges
 per vertex drawn (duplicates merged, 16,085,851 nonzeros), K = L = 128,
 seed 0.
@@ -48,14 +48,15 @@ if ROOT not in sys.path:
 
 HBM_PEAK_GBPS = 8000.0  # MI355X HBM3E, published
 METRIC = "fused SDDMM→SpMM Gnnz/s + achieved HBM GB/s vs peak, R-MAT 1M rows K=L=128"
-KERNEL_SOURCES = ["paper_2205_11622_amd/csrc/walker.hpp", "paper_2205_11622_amd/csrc/epilogue.hpp",
-                  "paper_2205_11622_amd/csrc/sparselnr.hip"]
+KERNEL_SOURCES = ["paper_2205_11622_amd/csrc/walker.hpp", "paper_2205_11622_amd/csrc/batch.hpp",
+                  "paper_2205_11622_amd/csrc/epilogue.hpp", "paper_2205_11622_amd/csrc/sparselnr.hip"]
 KERNELS = ("sddmm_spmm", "sddmm_spmm_gemm", "spmm_gemm", "spmmh_gemm", "dt")
 CPU_SECONDS = 10.0  # oracle passes are repeated until about this much wall time
 # Grid factors (resident grids per walk launch) tried for each library call
 # before the timed region; the timed call and each pass of the comparison run
-# at their own fastest one.
-GRID_FACTORS = (1, 2, 4, 8, 12, 16, 24, 32, 48, 64)
+# at their own fastest one.  0 is the library's automatic choice, what a caller
+# gets by default (and the only one in which waves share slices of wide rows).
+GRID_FACTORS = (0, 1, 2, 4, 8, 12, 16, 24, 32, 48, 64)
 TUNE_CALLS = 5
 # Untimed, waited-for calls before each timed region, in seconds of wall time.
 SETTLE_S = 0.05
@@ -174,6 +175,12 @@ def row_parity(got, ref, scale, tol=1e-4, chunk=65536):
     return worst, bad
 
 
+def walk_name(M, K, L):
+    """The walk kernel of a fused call: the fixed-width one at K = L = 64 and 128 from
+    1 GiB of D and E rows on, else the batch walk."""
+    return "walk_fast" if K == L and K in (64, 128) and 4 * M * (K + L) >= 1 << 30 else "walk_batch"
+
+
 def make_workload(kernel, config, dev):
     """Inputs on the device, the timed call, the comparison call, the byte model
     and the oracle leg for one kernel."""
@@ -213,7 +220,7 @@ def make_workload(kernel, config, dev):
                          "sparselnr_spmm, each pass at its own grid factor",
             bytes=p.model_bytes(), bytes_model="4(N+1) + 8 nnz + 4 nnz (K+L) + 4 N K + 4 N L",
             footprint=csr_bytes + 4 * (N * p.K + M * p.K + M * p.L + N * p.L),
-            dominant="walk_fast fused + carry_fixup (one call)", out=A,
+            dominant="%s fused + carry_fixup (one call)" % walk_name(M, p.K, p.L), out=A,
             oracle=lambda: __import__("oracle").fused_rows(p.rowptr, p.colidx, p.vals, p.C, p.D,
                                                            p.E))
 
@@ -327,7 +334,7 @@ def make_workload(kernel, config, dev):
             bytes=p.model_bytes() + 8 * M * p.K,
             bytes_model="8 M K (transpose pass) + 4(N+1) + 8 nnz + 4 nnz (K+L) + 4 N K + 4 N L",
             footprint=csr_bytes + 4 * (N * p.K + 2 * M * p.K + M * p.L + N * p.L),
-            dominant="transpose_kernel + walk_fast fused + carry_fixup (one call)", out=A,
+            dominant="transpose_kernel + %s fused + carry_fixup (one call)" % walk_name(M, p.K, p.L), out=A,
             oracle=lambda: __import__("oracle").fused_rows_dt(p.rowptr, p.colidx, p.vals, p.C,
                                                               Dth, p.E))
     raise ValueError(kernel)
@@ -439,7 +446,8 @@ def main() -> int:
                          "separate passes over K, L in {16..512} (one JSON line per point)")
     ap.add_argument("--grid-factor", default="auto",
                     help="resident grids per walk launch for the timed call: 'auto' (fastest "
-                         "of %s, chosen before the timed region) or a fixed value in 1..64"
+                         "of %s, chosen before the timed region) or a fixed value in 0..64 "
+                         "(0: the library's own choice)"
                          % ",".join(map(str, GRID_FACTORS)))
     ap.add_argument("--compare-grid-factor", default="auto",
                     help="the same for the comparison: 'auto', one value for every pass, or "
@@ -527,8 +535,8 @@ def main() -> int:
         vals = [int(x) for x in spec.split(",")]
         if len(vals) == 1:
             vals = vals * len(parts)
-        if len(vals) != len(parts) or not all(1 <= f <= 64 for f in vals):
-            raise SystemExit("%s: need 'auto' or %d value(s) in 1..64" % (what, len(parts)))
+        if len(vals) != len(parts) or not all(0 <= f <= 64 for f in vals):
+            raise SystemExit("%s: need 'auto' or %d value(s) in 0..64" % (what, len(parts)))
         return vals, None
 
     def bound(parts, factors):

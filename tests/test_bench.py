@@ -72,3 +72,14 @@ def test_row_parity_rule_of_the_bench_line():
     assert worst == np.inf
     worst_ok, bad_ok = bench.row_parity(got[20:], ref[20:], scale[20:], chunk=64)
     assert bad_ok == 0 and worst_ok == ratio[20:].max()
+
+
+def test_stored_counters_follow_every_kernel_source():
+    """The digest that keeps stored counters valid covers all device code and the
+    dispatch, and the factors tried include what a caller gets by default."""
+    import bench
+    csrc = os.path.join(ROOT, "paper_2205_11622_amd", "csrc")
+    assert sorted(os.path.basename(f) for f in bench.KERNEL_SOURCES) == sorted(os.listdir(csrc))
+    assert 0 in bench.GRID_FACTORS
+    assert bench.walk_name(1 << 20, 128, 128) == bench.walk_name(1 << 22, 64, 64) == "walk_fast"
+    assert bench.walk_name((1 << 20) - 1, 128, 128) == bench.walk_name(1 << 21, 16, 256) == "walk_batch"

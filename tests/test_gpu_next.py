@@ -230,7 +230,7 @@ def test_next_on_rmat1m(gpu, kernel):
     ref, scale = oracle_reference(fn, base.N, width, gpu)
     A = torch.empty((base.N, width), dtype=torch.float32, device=gpu)
     try:
-        for f in (0,) + tuple(bench.GRID_FACTORS):
+        for f in bench.GRID_FACTORS:
             slnr.sparselnr_set_grid_factor(f)
             what = "%s, grid factor %s" % (kernel, f or "automatic")
             A.fill_(float("nan"))
