@@ -57,8 +57,9 @@
  *     synchronisation or memset, and can be captured on that stream.  The
  *     graph records the workspace address: while it may still be replayed,
  *     do not call sparselnr_release() and make no call on that stream that
- *     needs a larger workspace (more rows, a wider L, a larger grid factor),
- *     since either frees the workspace.
+ *     needs a larger workspace (more rows, a larger grid factor, other widths
+ *     K and L or another entry point, which may take more workers), since
+ *     either frees the workspace.  Calls made once before the capture do not.
  *   - Results are deterministic: the same inputs give bit-identical outputs
  *     on the same device model (no floating-point atomics).
  *   - No C++ exception crosses this interface.
@@ -100,8 +101,10 @@ SPARSELNR_API int sparselnr_abi_version(void);
  * Fused SDDMM->SpMM (Figure 2d; Section 3.1.3):
  *   A(i,:) = sum_{p in row i} vals[p] * dot(C(i,:), D(colidx[p],:)) * E(colidx[p],:)
  * A is overwritten.  Arithmetic is fp32 (fused multiply-add), with the
- * k-reduction done as a lane-parallel tree and the l-update accumulated in
- * nonzero order.  Needs the per-(device, stream) workspace.
+ * k-reduction done as a lane-parallel tree.  The nonzeros of a row are added
+ * in an order fixed by its length, the widths and the grid: up to 16 partial
+ * sums side by side, long rows in groups of four, then the sums of the pieces
+ * of a split row in order.  Needs the per-(device, stream) workspace.
  */
 SPARSELNR_API int sparselnr_fused_sddmm_spmm(const int32_t *rowptr, const int32_t *colidx,
                                              const float *vals, const float *C,
@@ -256,7 +259,8 @@ SPARSELNR_API int sparselnr_last_hip_error(void);
  * narrower band of rows, which changes how D and E rows are shared in the
  * caches.  factor 0 restores the automatic choice (by the number of rows per
  * resident worker and the widths; 1 for small matrices; several waves may share
- * a slice of wide rows then); 1..64 fixes the factor for every
+ * a slice of wide rows then).  Where rows have a few nonzeros the device makes
+ * fewer, longer slices than there are workers.  1..64 fixes the factor for every
  * later call in the process, on every device and stream (the environment
  * variable SPARSELNR_GRID_FACTOR gives the first value).  Results are
  * deterministic for a fixed factor; another factor splits rows between slices

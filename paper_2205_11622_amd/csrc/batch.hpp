@@ -7,7 +7,8 @@
 // pass it adds y * E_j into the rows of A.  In both passes G lanes take four
 // floats each of a gathered row, so 64 / G nonzeros go side by side, and four
 // such gathers are issued before the first is used: of one row, or of two or
-// four short rows at once.  Lane count and column tile depend on the width
+// four short rows at once; rows of at most four nonzeros go one to a group of at
+// most eight lanes.  Lane count and column tile depend on the width
 // alone, at run time: every width from 1 to 256 floats takes one tile, a wider
 // one equal tiles.
 //
@@ -15,12 +16,14 @@
 // walks reach 58 lines of 128 bytes a nanosecond) and, for rows of a few
 // nonzeros, the instructions per row.  Measured on MI355X, us:
 //   one nonzero at a time, one float per lane (what odd widths had) -> batch:
-//     100003 power-law rows of 25, K = 100, L = 47: 604 -> 267 (16M lines touched, 60 a ns)
-//     SpMM, 300007 power-law rows of 20, L = 96: 894 -> 334
+//     100003 power-law rows of 25, K = 100, L = 47: 604 -> 269 (16M lines touched, 60 a ns)
+//     SpMM, 300007 power-law rows of 20, L = 96: 894 -> 323
 //   lane groups of a wave walking rows of their own (powers of two had) -> batch:
-//     150000 uniform rows of 24 at K = L = 64, D transposed first: 320 -> 269
-//     2^16 R-MAT vertices of 20 at K = L = 16: 165 -> 55, at 64: 125 -> 73
-//     27-point stencil of 101^3 at K = L = 64: 1815 -> 1020
+//     150000 uniform rows of 24 at K = L = 64: 302 -> 248
+//     2^17 R-MAT vertices of 20 at K = L = 16: 206 -> 93, 2^16 at 64: 126 -> 71
+//     27-point stencil of 114^3 at K = L = 64: 2640 -> 1690, at 16: 1136 -> 475
+//     (at 32 1075 -> 1265, 17% slower: rows of 27 fill 27 of the 32 places of a burst, and
+//     the planes just outgrow L2; 100^3 967 -> 832)
 //   whose groups wait for the longest row among them, and whose burst of one row
 //   ends before the next begins.
 // Where neighbouring rows share columns, the fabric is spared by few rows being
@@ -148,9 +151,10 @@ __device__ __forceinline__ void ld_cols(float (&r)[4], const float *base, uint32
 }
 
 // Parts of a slice of S items: `most` (odd), or the odd number that leaves about
-// kPartItems to each.  A part costs 5 to 7 us of its wave's time in searches and
+// kPartItems to each.  A part costs some 4 us of its wave's time in searches and
 // first loads.  us at parts of 80 / 64 items and at whole slices: 1M uniform rows of
 // 16 at K = L = 128 2870 / 2915 / 2744, SpMM at 256 with 1M rows of 4 918 / 1024 / 840.
+// Rounded down to an odd number the 75^3 stencil at K = 16, L = 256 takes 1130 for 810.
 constexpr uint32_t kPartItems = 80;
 
 __device__ __forceinline__ uint32_t parts_of(uint32_t S, uint32_t most) {
@@ -721,6 +725,8 @@ struct BatchWalk {
 // Four gathers in flight per lane and six waves per SIMD; eight gathers need
 // 120 registers and leave four.  SDDMM, with fewer registers, has seven: with six the
 // 27-point stencils take 11% longer at K = 32 (114^3 635 -> 704 us), if 25% less at 64.
+// The fused kernels keep 20 to 25 scalars in lanes of vector registers, those of ragged
+// widths 55 to 65, which costs them 1 to 3%.
 template <int MODE, bool TAIL, bool BIG>
 __global__ __launch_bounds__(64) 
     __attribute__((amdgpu_waves_per_eu(MODE == kSddmm ? 7 : 6))) void walk_batch(WalkArgs a) {
