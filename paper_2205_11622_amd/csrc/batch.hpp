@@ -501,10 +501,11 @@ struct BatchWalk {
         ib, pb, pe,
         [&](uint32_t row, uint32_t s, uint32_t e) {
           float acc[4] = {0.f, 0.f, 0.f, 0.f};
-          // Long segments halve their rounding error by it (SpMM at L = 96, power-law rows:
-          // 2.0e-7 -> 1.2e-7).  Widths to 64 spread a row over four groups and more, and
-          // there 65536 rows of 16 ran 1% slower with the test alone.
-          const bool tall = G >= 32 && (int)(e - s) > 4 * U * NPP;
+          // Long segments halve their rounding error by it (off the 64-bit values, without /
+          // with: SpMM of power-law rows of 20 at L = 96 2.0e-7 / 1.2e-7, at 64 1.4e-7 / 1.0e-7, of 4
+          // at 64 1.0e-7 / 7.8e-8, at 32 8.7e-8 / 7.5e-8) and no time: 65536 rows of 16 at K = L = 64
+          // 74.2 / 74.3 us, SpMM of 1M rows of 16 at 64 612 / 612.
+          const bool tall = (int)(e - s) > 2 * U * NPP;
           for (uint32_t k = s; k < e; k += U * NPP) {
             const int n = (int)(e - k);
             const int2 *zp = nz + (k - pb);

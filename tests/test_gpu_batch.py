@@ -231,3 +231,23 @@ def test_rows_of_a_few_nonzeros_over_batches(gpu):
         check_A_rows(p, Au, rows=rows, what="unfused")
     finally:
         slnr.sparselnr_set_grid_factor(0)
+
+
+@pytest.mark.parametrize("L", [16, 32, 64, 96])
+def test_long_sums_add_small_terms_first(gpu, L):
+    """A row's first nonzero in each lane group is 1, the others 2^-25, which added to 1 one by
+    one leave it as it is.  The four of a burst summed first make 2^-23 and count, but for
+    the three beside the 1: at most a quarter of the small terms is lost, not all."""
+    import torch
+    n, N = 256, 40_000  # rows that neither slices nor batches of 512 split
+    groups = 64 // max(4, min(64, 1 << ((L + 3) // 4 - 1).bit_length()))
+    vals = torch.full((N, n), 2.0 ** -25, device=gpu)
+    vals[:, :groups] = 1
+    rowptr = torch.arange(N + 1, dtype=torch.int32, device=gpu) * n
+    col = torch.zeros(N * n, dtype=torch.int32, device=gpu)
+    E, one = torch.ones(1, L, device=gpu), torch.ones(N, 1, device=gpu)
+    small = (n - groups) * 2.0 ** -25
+    for A in (slnr.sparselnr_spmm(rowptr, col, vals.view(-1), E),
+              slnr.sparselnr_fused_sddmm_spmm(rowptr, col, vals.view(-1), one, one[:1], E)):
+        err = (A.double() - (groups + small)).abs().max()
+        assert float(err) <= small / 4 + 2.0 ** -24 * groups, groups  # and the rounding of the sum itself
