@@ -12,11 +12,13 @@
 // alone, at run time: every width from 1 to 256 floats takes one tile, a wider
 // one equal tiles.
 //
-// What bounds it is the fabric that the L2 misses go through (plain streaming
-// walks reach 58 lines of 128 bytes a nanosecond) and, for rows of a few
-// nonzeros, the instructions per row.  Measured on MI355X, us:
+// What bounds it where columns are random is the fabric that the L2 misses go through
+// (counted: 40 to 49 lines of 128 bytes a nanosecond, 120 to 160 reads outstanding in
+// each channel of L2), for rows of a few nonzeros the instructions and the start of
+// each wave; the 128^3 stencil reads 29 lines a nanosecond, short of both.  Measured on
+// MI355X, us:
 //   one nonzero at a time, one float per lane (what odd widths had) -> batch:
-//     100003 power-law rows of 25, K = 100, L = 47: 604 -> 269 (16M lines touched, 60 a ns)
+//     100003 power-law rows of 25, K = 100, L = 47: 604 -> 269
 //     SpMM, 300007 power-law rows of 20, L = 96: 894 -> 323
 //   lane groups of a wave walking rows of their own (powers of two had) -> batch:
 //     150000 uniform rows of 24 at K = L = 64: 302 -> 248
