@@ -72,8 +72,9 @@ def run_large(gpu, N, n, M, K, L):
         assert bool((err <= (K + n + 2) * 2.0 ** -24 * scale.amax(1)).all()), factor
 
 
-def test_more_columns_than_24_bits(gpu):
-    run_large(gpu, 300, 20, (1 << 24) + 77, 3, 5)
+@pytest.mark.parametrize("n", [20, 3])
+def test_more_columns_than_24_bits(gpu, n):
+    run_large(gpu, 300, n, (1 << 24) + 77, 3, 5)
 
 
 # the sizes from which K = L = 64 and 128 keep kernels of their own and one column below
